@@ -54,7 +54,7 @@ enum {
   FPCF4_E_UNSUPPORTED = -2,   /* nmax or nbins beyond the compiled limits        */
   FPCF4_E_OUT_OF_MEMORY = -3, /* device allocation failed                         */
   FPCF4_E_DEVICE = -4,        /* a HIP runtime call or kernel launch failed       */
-  FPCF4_E_BUDGET = -5,        /* caller workspace smaller than fpcf4_plan() says  */
+  FPCF4_E_BUDGET = -5,        /* caller workspace smaller than fpcf4_plan_min()   */
   FPCF4_E_CANCELLED = -6      /* request cancelled                                */
 };
 
@@ -63,7 +63,8 @@ enum { FPCF4_MEM_HOST = 0, FPCF4_MEM_DEVICE = 1 };
 /* Arithmetic of the path.
  *  FPCF4_FP64       : every stage in binary64.
  *  FPCF4_MIXED_FP16 : pair multipoles accumulated in binary32 with blocked
- *                     summation into binary64; contraction on MFMA with
+ *                     summation into binary64 (from nmax 4 on over binary16
+ *                     hi/lo operands of 22 bits); contraction on MFMA with
  *                     fp16 hi/lo split operands and fp32 accumulation per
  *                     centre chunk; binary64 cross-chunk reduction,
  *                     degenerate-term subtraction and output.
@@ -338,6 +339,12 @@ typedef struct fpcf4_request fpcf4_request;
 fpcf4_status fpcf4_plan(const fpcf4_catalogue *cat, const fpcf4_bins *bins,
                         const fpcf4_options *opts, size_t *device_bytes,
                         int64_t *ntiles);
+
+/* The smallest workspace a request runs in: fpcf4_plan() bytes without the
+ * operand copies of the faster pair kernel (96 bytes per galaxy in the mixed
+ * paths).  fpcf4_request_create() takes any size from this one on. */
+fpcf4_status fpcf4_plan_min(const fpcf4_catalogue *cat, const fpcf4_bins *bins,
+                            const fpcf4_options *opts, size_t *device_bytes);
 
 /* Bind inputs and a caller workspace (device memory of at least the planned
  * size, 256-byte aligned).  Uploads the catalogue and builds the cell list

@@ -341,8 +341,11 @@ def profile_read() -> dict:
     return {k: getattr(p, k) for k, _ in _lib.Profile._fields_}
 
 
-def plan(n: int, edges, nmax: int, precision="fp64", ncenters=None, tile_centers: int = 0):
-    """(device_bytes, ntiles) a request with these sizes needs."""
+def plan(n: int, edges, nmax: int, precision="fp64", ncenters=None, tile_centers: int = 0,
+         smallest: bool = False):
+    """(device_bytes, ntiles) of a request with these sizes; with `smallest`
+    the bytes it runs in at least (without the operand copies of the faster
+    pair kernel)."""
     z = np.zeros(1)
     m = _Marshal(z, z, z, z, z, edges, nmax, precision, True, None, tile_centers, None)
     m.cat.n = int(n)
@@ -353,6 +356,8 @@ def plan(n: int, edges, nmax: int, precision="fp64", ncenters=None, tile_centers
     nbytes = C.c_size_t(0)
     ntiles = C.c_int64(0)
     check(lib().fpcf4_plan(*m.refs(), C.byref(nbytes), C.byref(ntiles)))
+    if smallest:
+        check(lib().fpcf4_plan_min(*m.refs(), C.byref(nbytes)))
     return int(nbytes.value), int(ntiles.value)
 
 
@@ -372,8 +377,7 @@ class Request:
         self.ntiles = int(ntiles.value)
         if workspace is None:
             workspace = torch.empty(self.bytes, dtype=torch.uint8, device="cuda")
-        if workspace.numel() < self.bytes:
-            raise Fpcf4Error(_lib.E_BUDGET, "workspace too small")
+        self.bytes = min(self.bytes, workspace.numel())   # too small a one is refused below
         self.workspace = workspace
         s = self.m.stream
         if s is not None and s != torch.cuda.current_stream(workspace.device).cuda_stream:

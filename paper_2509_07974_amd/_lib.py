@@ -92,6 +92,8 @@ def lib():
     L.fpcf4_to_natural.restype = C.c_int32
     L.fpcf4_plan.argtypes = [P(Catalogue), P(Bins), P(Options), P(C.c_size_t), P(C.c_int64)]
     L.fpcf4_plan.restype = C.c_int32
+    L.fpcf4_plan_min.argtypes = [P(Catalogue), P(Bins), P(Options), P(C.c_size_t)]
+    L.fpcf4_plan_min.restype = C.c_int32
     L.fpcf4_request_create.argtypes = [P(Catalogue), P(Bins), P(Options), C.c_void_p, C.c_size_t, P(C.c_void_p)]
     L.fpcf4_request_create.restype = C.c_int32
     L.fpcf4_request_step.argtypes = [C.c_void_p, C.c_int64]
@@ -136,7 +138,7 @@ def check(status: int):
 
 
 EXPORTED = [
-    "estimate_4pcf_multipoles", "fpcf4_debug_multipoles", "fpcf4_to_natural", "fpcf4_plan",
+    "estimate_4pcf_multipoles", "fpcf4_debug_multipoles", "fpcf4_to_natural", "fpcf4_plan", "fpcf4_plan_min",
     "fpcf4_request_create", "fpcf4_request_step", "fpcf4_request_finalize",
     "fpcf4_request_destroy", "fpcf4_last_error", "fpcf4_version", "fpcf4_output_elems",
     "fpcf4_profile_enable", "fpcf4_profile_read", "estimate_3pcf_multipoles", "fpcf4_output3_elems",

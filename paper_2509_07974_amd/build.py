@@ -3,8 +3,8 @@
     python -m paper_2509_07974_amd.build        # or __graft_entry__.build()
 
 Every HIP source is compiled to an object under ``_build/`` (in parallel;
-stage_a.hip once per supported nmax so its large unrolled kernels compile
-concurrently) and linked into ``paper_2509_07974_amd/libfpcf4.so``.
+stage_a.hip and stage_a_mfma.hip once per supported nmax so their large unrolled
+kernels compile concurrently) and linked into ``paper_2509_07974_amd/libfpcf4.so``.
 """
 from __future__ import annotations
 
@@ -52,13 +52,14 @@ def _jobs():
     hip = _hipcc()
     jobs = []
     for src in ("api.hip", "cells.hip", "stage_b.hip", "stage_b_pairs.hip", "natural.hip",
-                "threepcf.hip", "sort.hip", "stage_a.hip"):
+                "threepcf.hip", "sort.hip", "stage_a.hip", "stage_a_mfma.hip"):
         obj = os.path.join(BUILD, src.replace(".hip", ".o"))
         jobs.append([hip, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
     for n in range(NMAX_SUPPORTED + 1):
-        obj = os.path.join(BUILD, f"stage_a_n{n:02d}.o")
-        jobs.append([hip, *FLAGS, f"-DFPCF4_STAGE_A_N={n}", "-c",
-                     os.path.join(CSRC, "stage_a.hip"), "-o", obj])
+        for src in ("stage_a", "stage_a_mfma"):
+            obj = os.path.join(BUILD, f"{src}_n{n:02d}.o")
+            jobs.append([hip, *FLAGS, f"-DFPCF4_STAGE_A_N={n}", "-c",
+                         os.path.join(CSRC, f"{src}.hip"), "-o", obj])
     return jobs
 
 

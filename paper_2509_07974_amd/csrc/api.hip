@@ -11,8 +11,8 @@
 #include "fpcf4_internal.hpp"
 
 namespace fpcf4 {
-hipError_t cells_bbox(const double*, const double*, const double*, const double*, const double*,
-                      int64_t, double*, unsigned*, double*, hipStream_t);
+hipError_t cells_stats(const double*, const double*, const double*, const double*, const double*,
+                       int64_t, double*, unsigned*, double*, hipStream_t);
 size_t cells_sort_temp_bytes(int64_t n);
 hipError_t cells_build(const double*, const double*, const double*, const double*, const double*,
                        int64_t, const Grid&, uint32_t*, uint32_t*, int32_t*, int32_t*, void*, size_t,
@@ -60,9 +60,9 @@ constexpr size_t kTileRecordBudget = size_t(32) << 30;
 // work items; their number is cut so the partials stay below this many bytes
 // (one slice at least: at 65 bins and nmax 15 one slice is about 10 GB).
 constexpr size_t kPairPartialBudget = size_t(48) << 30;
-// Scheduling counters of stage (a) (8 per launch, two launches), then the
-// per-bin scaling maxima.
-constexpr int kSchedCounters = 128;
+// Scheduling counters of stage (a) (two launches), then the per-bin scaling
+// maxima.
+constexpr int kSchedCounters = 2 * SCHED_WORDS;
 constexpr int kCounterWords = kSchedCounters + MAXIMA_WORDS;
 
 struct PlanInfo {
@@ -77,7 +77,7 @@ struct PlanInfo {
   size_t sort_tmp = 0;
   // persistent buffers
   size_t o_gal, o_cells, o_centres, o_e2, o_edges, o_counters, o_bbox, o_bad,
-      o_pairs, o_part, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
+      o_pairs, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
       o_aos, o_region, o_pitems, o_pout, o_ppart, o_csums, o_cmap;
   // contraction work items (each distinct product of three blocks once)
   int pslices = 0;
@@ -92,6 +92,8 @@ struct PlanInfo {
   size_t region = 0;           // records of one tile, or create-time temporaries
   // create-time temporaries inside the region
   size_t t_raw, t_key_a, t_key_b, t_idx_a, t_idx_b, t_inv, t_sort, t_cent64;
+  size_t base = 0;             // workspace without the octets
+  size_t o_octets[TREE_LEVELS_MAX + 1] = {};   // octets of the matrix-core pair kernel
   size_t total = 0;
 };
 
@@ -180,10 +182,9 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.o_e2 = take((P.nb + 1) * 8);
   P.o_edges = take((P.nb + 1) * 8);
   P.o_counters = take(kCounterWords * 4);   // scheduling counters, then the scaling maxima
-  P.o_bbox = take(4 * 8);
+  P.o_bbox = take(kCatStats * 8);
   P.o_bad = take(16);
   P.o_pairs = take(16);
-  P.o_part = take(256 * 4 * 8);
   P.ups_bytes = order == 4 ? (size_t)9 * P.nb * P.nb * P.nb * nn * nn * 16 : 0;
   P.corr_bytes = order == 4 ? corr_elems(P.nb, P.nmax) * 16 : 0;
   P.acc3_bytes = order == 3 ? three_elems(P.nb, m3) * 16 : 0;
@@ -237,6 +238,11 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   if (P.tree_levels > 0) P.t_red = ttake(reduced_scratch_bytes(n));
   P.region = std::max(t, up((size_t)P.ldc * rec_per_centre));
   P.o_region = take(P.region);
+  P.base = off;
+  // octets of the matrix-core pair kernel (mixed paths), last, so that
+  // a workspace without room for them still serves with the vector kernel
+  if (P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax))
+    for (int d = 0; d <= P.tree_levels; ++d) P.o_octets[d] = take(octet_bytes(n));
   P.total = off;
   return FPCF4_OK;
 }
@@ -279,6 +285,9 @@ struct fpcf4_request {
   hipStream_t stream = nullptr;
   char* ws = nullptr;
   Grid grid{};
+  std::vector<double> edges;
+  bool mm[TREE_LEVELS_MAX + 1] = {};        // octets built for the galaxies / reduced catalogue d
+  MatScale ms[TREE_LEVELS_MAX + 1] = {};
   std::vector<char> stepped;
   PairPlanHost pplan;           // the contraction plan uploaded into the workspace (4PCF)
   CorrPlanHost cplan;           // the distinct degenerate-term sums, likewise
@@ -295,6 +304,55 @@ struct fpcf4_request {
 
 namespace {
 
+// The scales of the matrix-core pair kernel for a catalogue, or false where
+// the vector kernel has to serve.  Every operand is two binary16 values, 22
+// significant bits with an absolute floor of 2^-25.  The scales put w g and w
+// below 2^7 and their squares below 2^15, and the triple-block weights below
+// 2^15, so the floors are 2^-32, 2^-40 and 2^-40 of the largest value of
+// each.  binary32 has no such floor, so the matrix cores take catalogues whose
+// largest weight is at most 2^5 times its rms: every floor is then at most
+// 2^-24 of the rms of its own weight, as for binary32 rounding.  The kernel's
+// 32-bit byte offsets reach kMatrixMax neighbours.
+constexpr int64_t kMatrixMax = int64_t(1) << 25;
+static_assert(kMatrixMax / 8 * OCTET_BYTES <= (int64_t(1) << 32), "32-bit octet offsets");
+int exponent_above(double v) {   // v < 2^e
+  int e = 0;
+  if (v > 0.0) std::frexp(v, &e);
+  return e;
+}
+bool matrix_scale(const double* st, int64_t n, MatScale& m) {
+  if (n >= kMatrixMax) return false;
+  const double big[2] = {st[4], st[5]}, sq[2] = {st[6], st[7]};
+  for (int k = 0; k < 2; ++k) {
+    if (big[k] == 0.0) continue;
+    if (!(big[k] > 1e-9 && big[k] < 1e9)) return false;
+    if (!(big[k] * big[k] * (double)n <= 1024.0 * sq[k])) return false;
+  }
+  const int eg = exponent_above(big[0]), ew = exponent_above(big[1]);
+  // two components below 2^eg: (w g)^2 and |w g|^2 below 2^(2 eg + 1), the
+  // triple-block weights below 2^(3 eg + 1.5)
+  const int lg = 7 - eg, lw = 7 - ew;
+  const int ex[NWEIGHTS] = {lg, lg, 2 * lg, 2 * lg, lw, 2 * lg, 2 * lw,
+                            13 - 3 * eg, 13 - 3 * eg, 13 - 3 * eg, 13 - 3 * eg, 14 - 3 * ew};
+  for (int f = 0; f < NWEIGHTS; ++f) m.inv[f] = std::ldexp(1.0, -ex[f]);
+  return true;
+}
+// The same for a reduced catalogue, whose weights are cell sums with a
+// largest value of their own each (at most 2^12 times its rms).
+bool matrix_scale_reduced(const double* st, int64_t m, MatScale& s) {
+  if (m >= kMatrixMax) return false;
+  for (int f = 0; f < NWEIGHTS; ++f) {
+    const double big = st[f];
+    if (big != 0.0) {
+      if (!(big > 1e-27 && big < 1e27)) return false;
+      if (!(big * big * (double)m <= 16777216.0 * st[NWEIGHTS + f])) return false;
+    }
+    const int ex = 15 - exponent_above(big);
+    s.inv[f] = std::ldexp(1.0, -ex);
+  }
+  return true;
+}
+
 fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
                           const fpcf4_options* opts, void* wsp, size_t bytes, fpcf4_request* R,
                           int order = 4, int m3 = 0, const fpcf4_tree* tree = nullptr) {
@@ -303,7 +361,9 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   if (st != FPCF4_OK) return st;
   if (!wsp) return fail(FPCF4_E_INVALID_ARG, "null workspace");
   if (reinterpret_cast<uintptr_t>(wsp) % ALIGN) return fail(FPCF4_E_INVALID_ARG, "workspace not 256-byte aligned");
-  if (bytes < P.total) return fail(FPCF4_E_BUDGET, "workspace %zu bytes < planned %zu", bytes, P.total);
+  if (bytes < P.base) return fail(FPCF4_E_BUDGET, "workspace %zu bytes < planned %zu", bytes, P.base);
+  const bool octets = P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax) && bytes >= P.total;
+  R->edges.assign(bins->edges, bins->edges + P.nb + 1);
   R->ws = static_cast<char*>(wsp);
   R->stream = static_cast<hipStream_t>(opts->stream);
   R->stepped.assign((size_t)P.ntiles, 0);
@@ -368,10 +428,11 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   }
   unsigned* bad = R->at<unsigned>(P.o_bad);
   HIPCHK(hipMemsetAsync(bad, 0, 16, s));
-  HIPCHK(cells_bbox(x, y, g1, g2, w, n, R->at<double>(P.o_part), bad, R->at<double>(P.o_bbox), s));
-  double bb[4];
+  HIPCHK(cells_stats(x, y, g1, g2, w, n, reinterpret_cast<double*>(reg + P.t_key_a), bad,
+                     R->at<double>(P.o_bbox), s));
+  double bb[kCatStats];
   unsigned hbad = 0;
-  HIPCHK(hipMemcpyAsync(bb, R->ws + P.o_bbox, 32, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(bb, R->ws + P.o_bbox, sizeof bb, hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   if (hbad) return fail(FPCF4_E_INVALID_ARG, "catalogue has %u non-finite entries", hbad);
@@ -380,10 +441,13 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   // tables of 64), capped cell count.  Finer cells walk fewer candidates
   // outside the bin, for more and shorter row segments (10^6 galaxies on
   // 600x600 arcmin, 12 bins 1-100: 1.14 candidates per in-bin pair, 1.28 at
-  // outer edge / 24).
+  // outer edge / 24).  A row segment of the matrix-core kernel costs about
+  // seven candidates of rounding to octets: with 3.2 e / h segments and
+  // 6.7 e h candidates per unit density outside an annulus of outer edge e the
+  // cost is least at 1.8 galaxies per cell, which sparse catalogues get.
   const double rmax = bins->edges[P.nb];
-  double h = rmax / 48.0;
   const double wx = bb[1] - bb[0], wy = bb[3] - bb[2];
+  double h = std::max(rmax / 48.0, std::min(1.35 * std::sqrt(wx * wy / (double)n), rmax / 8.0));
   for (;;) {
     const double ncx = std::floor(wx / h) + 1.0, ncy = std::floor(wy / h) + 1.0;
     if (ncx * ncy <= (double)P.ncell_cap) break;
@@ -418,15 +482,33 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     HIPCHK(cells_centre_order(key_b, n, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a, centres,
                               sort_tmp, P.sort_tmp, s));
   }
+  if (octets && matrix_scale(bb, n, R->ms[0])) {
+    HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->ws + P.o_octets[0], s));
+    R->mm[0] = true;
+  }
   // reduced catalogues of the tree approximation, on the same search grid
   for (int d = 1; d <= P.tree_levels; ++d) {
     int64_t m = 0;
+    double st[2 * NWEIGHTS];
     HIPCHK(reduced_build(x, y, g1, g2, w, n, bb[0], bb[2], bb[1], bb[3],
                          P.tree_delta1 * std::ldexp(1.0, d - 1), g, reg + P.t_red,
-                         R->ws + P.o_rgal[d - 1], R->at<int32_t>(P.o_rcell[d - 1]), &m, s));
+                         R->ws + P.o_rgal[d - 1], R->at<int32_t>(P.o_rcell[d - 1]), &m, s, nullptr, st));
+    if (octets && m > 0 && matrix_scale_reduced(st, m, R->ms[d])) {
+      HIPCHK(build_octets(R->at<GalR<float>>(P.o_rgal[d - 1]), m, R->ms[d], R->ws + P.o_octets[d], s));
+      R->mm[d] = true;
+    }
   }
   HIPCHK(hipStreamSynchronize(s));
   return FPCF4_OK;
+}
+
+// neighbours of the pair kernels: the matrix-core kernel's operands
+void matrix_args(const fpcf4_request* R, StageAArgs& a) {
+  for (int d = 0; d <= R->P.tree_levels; ++d) {
+    a.octets[d] = R->mm[d] ? R->ws + R->P.o_octets[d] : nullptr;
+    a.ms[d] = R->ms[d];
+  }
+  a.host_edges = R->edges.data();
 }
 
 fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
@@ -478,6 +560,7 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
     a.rgal[d - 1] = R->ws + P.o_rgal[d - 1];
     a.rcell[d - 1] = R->at<int32_t>(P.o_rcell[d - 1]);
   }
+  matrix_args(R, a);
   int nlaunch = 0;
   if (P.precision == FPCF4_FP64) HIPCHK(launch_stage_a<double>(P.nmax, P.order, a, s, &nlaunch, evs[1]));
   else HIPCHK(launch_stage_a<float>(P.nmax, P.order, a, s, &nlaunch, evs[1]));
@@ -738,6 +821,7 @@ fpcf4_status run_3pcf_basetree(fpcf4_request* R, const fpcf4_catalogue* cat, con
       a.rgal[t - 1] = R->ws + P.o_rgal[t - 1];
       a.rcell[t - 1] = R->at<int32_t>(P.o_rcell[t - 1]);
     }
+    matrix_args(R, a);
     int nl = 0;
     if (G[d].m > 0) HIPCHK(launch_stage_a<float>(P.nmax, 3, a, s, &nl, nullptr));
   }
@@ -788,6 +872,15 @@ fpcf4_status fpcf4_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins, cons
   if (st != FPCF4_OK) return st;
   if (device_bytes) *device_bytes = P.total;
   if (ntiles) *ntiles = P.ntiles;
+  return FPCF4_OK;
+}
+
+fpcf4_status fpcf4_plan_min(const fpcf4_catalogue* cat, const fpcf4_bins* bins, const fpcf4_options* opts,
+                            size_t* device_bytes) {
+  PlanInfo P;
+  fpcf4_status st = make_plan(cat, bins, opts, P);
+  if (st != FPCF4_OK) return st;
+  if (device_bytes) *device_bytes = P.base;
   return FPCF4_OK;
 }
 
@@ -908,15 +1001,15 @@ fpcf4_status estimate_4pcf_multipoles_noalloc(const fpcf4_catalogue* cat, const 
   fpcf4_status st = make_plan(cat, bins, opts, P);
   if (st != FPCF4_OK) return st;
   fpcf4_options o = *opts;
-  if (P.total > FPCF4_NOALLOC_SCRATCH_BYTES && opts->tile_centers == 0) {
+  if (P.base > FPCF4_NOALLOC_SCRATCH_BYTES && opts->tile_centers == 0) {
     // smaller centre tiles shrink the per-tile record buffers
-    for (int64_t tile = P.tile / 2; tile >= 64 && P.total > FPCF4_NOALLOC_SCRATCH_BYTES; tile /= 2) {
+    for (int64_t tile = P.tile / 2; tile >= 64 && P.base > FPCF4_NOALLOC_SCRATCH_BYTES; tile /= 2) {
       o.tile_centers = tile;
       if ((st = make_plan(cat, bins, &o, P)) != FPCF4_OK) return st;
     }
   }
-  if (P.total > FPCF4_NOALLOC_SCRATCH_BYTES)
-    return fail(FPCF4_E_BUDGET, "workspace of %zu bytes exceeds the static scratch of %zu bytes", P.total,
+  if (P.base > FPCF4_NOALLOC_SCRATCH_BYTES)
+    return fail(FPCF4_E_BUDGET, "workspace of %zu bytes exceeds the static scratch of %zu bytes", P.base,
                 (size_t)FPCF4_NOALLOC_SCRATCH_BYTES);
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));

@@ -1,7 +1,8 @@
 // Spatial sort of the catalogue into a row-major cell grid (the neighbour
 // search structure of stage (a)), and the centre order.
 //
-//  bbox_kernel    : min/max of x and y and a count of non-finite inputs
+//  stats kernels  : min/max of x and y, the weights' maxima and sums of squares,
+//                   and a count of non-finite inputs
 //  key_kernel     : cell key cy * ncx + cx of every galaxy
 //  (radix_sort_pairs of (key, index) pairs: stable, deterministic)
 //  starts_kernel  : cell_start[c] = first sorted position of cell c
@@ -10,62 +11,76 @@
 //  morton_kernel  : Morton key of each sorted galaxy's cell, so that the
 //                   centre list (sorted by it) visits space in compact blocks
 #include <algorithm>
+#include <vector>
 
 #include "fpcf4_internal.hpp"
 
 namespace fpcf4 {
 
-__global__ void bbox_partial_kernel(const double* x, const double* y, const double* g1,
-                                    const double* g2, const double* w, int64_t n,
-                                    double* part /* [nblk][4] */, unsigned* bad) {
-  __shared__ double s[4][256];
-  double mnx = INFINITY, mxx = -INFINITY, mny = INFINITY, mxy = -INFINITY;
+// Per block: min / max of x and y, max |w g| component, max |w|, sum |w g|^2,
+// sum w^2 (kCatStats values), and the count of non-finite galaxies, which
+// enter nothing else.
+__device__ __forceinline__ void stat_join(double* a, const double* b) {
+  a[0] = fmin(a[0], b[0]);
+  a[1] = fmax(a[1], b[1]);
+  a[2] = fmin(a[2], b[2]);
+  a[3] = fmax(a[3], b[3]);
+  a[4] = fmax(a[4], b[4]);
+  a[5] = fmax(a[5], b[5]);
+  a[6] += b[6];
+  a[7] += b[7];
+}
+// over the workgroup (256 threads), in a fixed order; thread 0 ends with all
+__device__ __forceinline__ void stat_block(double* v) {
+  __shared__ double s[4][kCatStats];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    double o[kCatStats];
+#pragma unroll
+    for (int k = 0; k < kCatStats; ++k) o[k] = __shfl_xor(v[k], d, 64);
+    stat_join(v, o);
+  }
+  const int wv = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < kCatStats; ++k) s[wv][k] = v[k];
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int w = 1; w < 4; ++w) stat_join(v, s[w]);
+}
+
+__global__ __launch_bounds__(256) void stats_partial_kernel(const double* x, const double* y, const double* g1,
+                                                            const double* g2, const double* w, int64_t n,
+                                                            double* part /* [nblk][kCatStats] */, unsigned* bad) {
+  double v[kCatStats] = {INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
   unsigned nbad = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const double xv = x[i], yv = y[i];
-    if (!isfinite(xv) || !isfinite(yv) || !isfinite(g1[i]) || !isfinite(g2[i]) || !isfinite(w[i])) {
+    const double xv = x[i], yv = y[i], wv = w[i], a = g1[i], b = g2[i];
+    if (!isfinite(xv) || !isfinite(yv) || !isfinite(a) || !isfinite(b) || !isfinite(wv)) {
       ++nbad;
       continue;
     }
-    mnx = fmin(mnx, xv);
-    mxx = fmax(mxx, xv);
-    mny = fmin(mny, yv);
-    mxy = fmax(mxy, yv);
+    const double ga = fabs(wv * a), gb = fabs(wv * b);
+    const double o[kCatStats] = {xv, xv, yv, yv, fmax(ga, gb), fabs(wv), ga * ga + gb * gb, wv * wv};
+    stat_join(v, o);
   }
-  s[0][threadIdx.x] = mnx;
-  s[1][threadIdx.x] = mxx;
-  s[2][threadIdx.x] = mny;
-  s[3][threadIdx.x] = mxy;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) {
-      s[0][threadIdx.x] = fmin(s[0][threadIdx.x], s[0][threadIdx.x + st]);
-      s[1][threadIdx.x] = fmax(s[1][threadIdx.x], s[1][threadIdx.x + st]);
-      s[2][threadIdx.x] = fmin(s[2][threadIdx.x], s[2][threadIdx.x + st]);
-      s[3][threadIdx.x] = fmax(s[3][threadIdx.x], s[3][threadIdx.x + st]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    for (int k = 0; k < 4; ++k) part[blockIdx.x * 4 + k] = s[k][0];
-  }
+  stat_block(v);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < kCatStats; ++k) part[blockIdx.x * kCatStats + k] = v[k];
   if (nbad) atomicAdd(bad, nbad);
 }
 
-__global__ void bbox_final_kernel(const double* part, int nblk, double* out) {
-  if (threadIdx.x != 0) return;
-  double mnx = INFINITY, mxx = -INFINITY, mny = INFINITY, mxy = -INFINITY;
-  for (int b = 0; b < nblk; ++b) {
-    mnx = fmin(mnx, part[4 * b + 0]);
-    mxx = fmax(mxx, part[4 * b + 1]);
-    mny = fmin(mny, part[4 * b + 2]);
-    mxy = fmax(mxy, part[4 * b + 3]);
+__global__ __launch_bounds__(256) void stats_final_kernel(const double* part, int nblk, double* out) {
+  double v[kCatStats] = {INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
+  for (int b = threadIdx.x; b < nblk; b += 256) {
+    double o[kCatStats];
+#pragma unroll
+    for (int k = 0; k < kCatStats; ++k) o[k] = part[b * kCatStats + k];
+    stat_join(v, o);
   }
-  out[0] = mnx;
-  out[1] = mxx;
-  out[2] = mny;
-  out[3] = mxy;
+  stat_block(v);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < kCatStats; ++k) out[k] = v[k];
 }
 
 __device__ __forceinline__ int cell_of(double v, double v0, double inv_h, int nc) {
@@ -147,12 +162,14 @@ static inline int grid1d(int64_t n) {
   return (int)b;
 }
 
-hipError_t cells_bbox(const double* x, const double* y, const double* g1, const double* g2,
-                      const double* w, int64_t n, double* part, unsigned* bad, double* out,
-                      hipStream_t s) {
-  const int nblk = 256;
-  hipLaunchKernelGGL(bbox_partial_kernel, dim3(nblk), dim3(256), 0, s, x, y, g1, g2, w, n, part, bad);
-  hipLaunchKernelGGL(bbox_final_kernel, dim3(1), dim3(64), 0, s, part, nblk, out);
+// out[kCatStats] as stats_partial_kernel lists them; part holds
+// kCatStats doubles for each of up to max(1, n / 256) blocks.
+hipError_t cells_stats(const double* x, const double* y, const double* g1, const double* g2,
+                       const double* w, int64_t n, double* part, unsigned* bad, double* out,
+                       hipStream_t s) {
+  const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>(2048, n / 256));
+  hipLaunchKernelGGL(stats_partial_kernel, dim3(nblk), dim3(256), 0, s, x, y, g1, g2, w, n, part, bad);
+  hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(256), 0, s, part, nblk, out);
   return hipGetLastError();
 }
 
@@ -277,6 +294,38 @@ __global__ void rsum_kernel(const double* x, const double* y, const double* g1, 
   }
 }
 
+// largest |value| and sum of squares of every weight over the cells:
+// part[block][2 NWEIGHTS], maxima first, in the order of MatScale
+__global__ __launch_bounds__(256) void rstats_kernel(const double* pd, int64_t ldp, const int32_t* head,
+                                                     const int32_t* segid, int64_t n, double* part) {
+  static const int field[NWEIGHTS] = {2, 3, 4, 5, 8, 6, 7, 9, 10, 11, 12, 13};
+  const int64_t m = (int64_t)segid[n - 1] + head[n - 1];
+  __shared__ double s[2][256];
+  for (int f = 0; f < NWEIGHTS; ++f) {
+    double mx = 0.0, sq = 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+      const double v = pd[field[f] * ldp + i];
+      mx = fmax(mx, fabs(v));
+      sq += v * v;
+    }
+    s[0][threadIdx.x] = mx;
+    s[1][threadIdx.x] = sq;
+    __syncthreads();
+    for (int st = 128; st > 0; st >>= 1) {
+      if ((int)threadIdx.x < st) {
+        s[0][threadIdx.x] = fmax(s[0][threadIdx.x], s[0][threadIdx.x + st]);
+        s[1][threadIdx.x] += s[1][threadIdx.x + st];
+      }
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+      part[blockIdx.x * 2 * NWEIGHTS + f] = s[0][0];
+      part[blockIdx.x * 2 * NWEIGHTS + NWEIGHTS + f] = s[1][0];
+    }
+    __syncthreads();
+  }
+}
+
 __global__ void rgather_kernel(const double* pd, int64_t ldp, const int32_t* perm, int64_t m,
                                GalR<float>* out) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m;
@@ -316,8 +365,9 @@ __global__ void rmember_kernel(const int32_t* ib, const int32_t* head, const int
 }
 
 namespace {
+constexpr int kRedStatBlocks = 64;
 struct RedLayout {
-  size_t k64a, k64b, ia, ib, head, segid, segstart, pd, ka, kb, pa, pb, tmp, tmp_bytes, total;
+  size_t k64a, k64b, ia, ib, head, segid, segstart, pd, ka, kb, pa, pb, st, tmp, tmp_bytes, total;
 };
 RedLayout red_layout(int64_t n) {
   const int64_t nn = n > 0 ? n : 1;
@@ -338,6 +388,7 @@ RedLayout red_layout(int64_t n) {
   L.kb = take(nn * 4);
   L.pa = take(nn * 4);
   L.pb = take(nn * 4);
+  L.st = take((size_t)kRedStatBlocks * 2 * NWEIGHTS * 8);
   L.tmp_bytes = std::max(tsort, tsc);
   L.tmp = take(L.tmp_bytes);
   L.total = o;
@@ -350,7 +401,7 @@ size_t reduced_scratch_bytes(int64_t n) { return red_layout(n).total; }
 hipError_t reduced_build(const double* x, const double* y, const double* g1, const double* g2,
                          const double* w, int64_t n, double x0, double y0, double xmax, double ymax,
                          double delta, const Grid& g, void* scratch, void* gal_out,
-                         int32_t* cell_start, int64_t* m_out, hipStream_t s, int32_t* member) {
+                         int32_t* cell_start, int64_t* m_out, hipStream_t s, int32_t* member, double* stats) {
   *m_out = 0;
   if (n <= 0) return hipSuccess;
   const RedLayout L = red_layout(n);
@@ -384,11 +435,27 @@ hipError_t reduced_build(const double* x, const double* y, const double* g1, con
   hipLaunchKernelGGL(rsum_kernel, dim3(grid1d(n)), dim3(256), 0, s, x, y, g1, g2, w, ib, head, segid,
                      segstart, n, pd);
   int32_t hm[2] = {0, 0};
+  std::vector<double> hst;
+  if (stats != nullptr) {
+    double* st = reinterpret_cast<double*>(at(L.st));
+    hst.resize((size_t)kRedStatBlocks * 2 * NWEIGHTS);
+    hipLaunchKernelGGL(rstats_kernel, dim3(kRedStatBlocks), dim3(256), 0, s, pd, n, head, segid, n, st);
+    e = hipMemcpyAsync(hst.data(), st, hst.size() * 8, hipMemcpyDeviceToHost, s);
+    if (e != hipSuccess) return e;
+  }
   e = hipMemcpyAsync(&hm[0], segid + (n - 1), 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipMemcpyAsync(&hm[1], head + (n - 1), 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
   const int64_t m = (int64_t)hm[0] + hm[1];
+  if (stats != nullptr) {
+    for (int k = 0; k < 2 * NWEIGHTS; ++k) stats[k] = 0.0;
+    for (int b = 0; b < kRedStatBlocks; ++b)
+      for (int f = 0; f < NWEIGHTS; ++f) {
+        stats[f] = std::max(stats[f], hst[(size_t)b * 2 * NWEIGHTS + f]);
+        stats[NWEIGHTS + f] += hst[(size_t)b * 2 * NWEIGHTS + NWEIGHTS + f];
+      }
+  }
   // search-grid order of the pseudo-galaxies, cell starts, records
   const int64_t ncells = (int64_t)g.ncx * g.ncy;
   hipLaunchKernelGGL(key_kernel, dim3(grid1d(m)), dim3(256), 0, s, pd, pd + n, m, g, ka, pa);

@@ -42,7 +42,7 @@ struct Layout {
 __host__ __device__ constexpr int imax(int a, int b) { return a > b ? a : b; }
 __host__ __device__ constexpr int imin(int a, int b) { return a < b ? a : b; }
 
-__host__ __device__ inline Layout make_layout(int n) {
+__host__ __device__ constexpr Layout make_layout(int n) {
   Layout L{};
   L.n = n;
   L.qlo = imin(-2 * n - 5, -n - 6);
@@ -116,6 +116,10 @@ __host__ __device__ inline BinTiles bin_tiles(int nb) {
   return BinTiles{nt > 0 ? (nb + nt - 1) / nt : 0, nt};
 }
 
+// Catalogue statistics: min x, max x, min y, max y, max |w g| component,
+// max |w|, sum |w g|^2, sum w^2.
+constexpr int kCatStats = 8;
+
 // Sorted catalogue on the device.
 struct SortedCat {
   int64_t n;
@@ -123,6 +127,36 @@ struct SortedCat {
   const int32_t* cell_start;  // [ncx*ncy + 1]
   Grid g;
 };
+
+// Operands of the matrix-core pair kernel (stage_a_mfma.hip).  Per weight of a
+// neighbour (Re, Im w g, Re, Im (w g)^2, w, |w g|^2, w^2, then the triple-block
+// weights Re, Im (w g)^3, Re, Im |w g|^2 w g, w^3) a power-of-two scale that
+// keeps its values below 2^15; f and inv are each other's inverses.
+constexpr int NWEIGHTS = 12;
+// Record orders that it serves.  Its cost steps with the number of its row
+// orders (one up to orders k = 25, two above), the vector kernel's grows with
+// every order: 1e5 galaxies at 2.5 per square arcmin, 12 bins 1-80', vector /
+// matrix kernel: 4PCF nmax 3 26.3 / 28.3 ms, 4 29.1 / 31.3, 5 37.2 / 31.5, 8
+// 43.7 / 31.6, 10 49.5 / 32.3; 3PCF records of order 7 26.7 / 27.6, 8 28.5 /
+// 27.9, 11 32.8 / 27.9, 12 34.3 / 36.1, 13 45.7 / 36.5, 16 52.4 / 38.3.
+__host__ __device__ constexpr bool matrix_order(int order, int n) {
+  return order == 3 ? n >= 8 && n != 12 : n >= 5;
+}
+struct MatScale {
+  double inv[NWEIGHTS];   // reciprocals of the scales
+};
+// Operands of 8 consecutive neighbours (an octet): positions, weights and
+// triple-block weights in the layout the kernel loads.
+constexpr int OCTET_BYTES = 768;   // a multiple of 256: the low byte of an offset carries a mask
+size_t octet_bytes(int64_t n);     // of n neighbours
+template <typename Rec>
+hipError_t build_octets(const Rec* gal, int64_t n, const MatScale& ms, void* out, hipStream_t s);
+
+// Stage (a) hands out centres from one queue per XCD.  Device-scope atomics on
+// one line are served one after the other by the memory side (about 12 ns each
+// measured), so every counter has a line of its own.
+constexpr int SCHED_STRIDE = 32;                  // words between the counters of two XCDs
+constexpr int SCHED_WORDS = 8 * SCHED_STRIDE;     // counters of one launch
 
 struct StageAArgs {
   SortedCat cat;
@@ -139,7 +173,7 @@ struct StageAArgs {
   void* xw;                 // [ldc] (T): w of each tile centre
   unsigned* maxima;         // scaling maxima (float bits, MAXIMA_* layout) or null
   int32_t* counts;          // [ncent][nb] or null
-  int32_t* work_counter;    // dynamic centre scheduling counters, one per XCD
+  int32_t* work_counter;    // dynamic centre scheduling counters, one per XCD (SCHED_STRIDE apart)
   unsigned long long* pairs;  // in-bin pair counter (may be null)
   int32_t b_lo, b_hi;       // bins to accumulate: [b_lo, b_hi); the rest are left alone
   // tree approximation: bins with level[b] = d >= 1 take their neighbours
@@ -147,6 +181,13 @@ struct StageAArgs {
   int8_t level[FPCF4_NBINS_SUPPORTED];
   const void* rgal[TREE_LEVELS_MAX];         // GalR<float>, sorted by search cell
   const int32_t* rcell[TREE_LEVELS_MAX];     // their cell starts
+  // matrix-core kernel of the binary32 records: octets and scales of the
+  // galaxies (0) and of reduced catalogue d; null: the vector kernel
+  const void* octets[TREE_LEVELS_MAX + 1];
+  MatScale ms[TREE_LEVELS_MAX + 1];
+  const double* host_edges;                  // host copy of edges, for the launcher
+  int32_t ngroups;                           // bin groups, set by the launcher
+  uint8_t gfirst[FPCF4_NBINS_SUPPORTED + 1], gend[FPCF4_NBINS_SUPPORTED + 1];
 };
 
 // Stable radix sort of (key, value) pairs on the low `bits` bits of the keys
@@ -169,11 +210,14 @@ hipError_t exclusive_scan_i32(void* tmp, size_t tmp_bytes, const int32_t* in, in
 // starts.  Scratch is caller-provided (reduced_scratch_bytes); returns the
 // number of pseudo-galaxies in *m (host, after a stream synchronisation).
 // member (optional, [n]): the pseudo-galaxy of every galaxy (catalogue order).
+// stats (optional, host, [2 NWEIGHTS]): largest |value| of every weight over
+// the pseudo-galaxies, then their sums of squares.
 size_t reduced_scratch_bytes(int64_t n);
 hipError_t reduced_build(const double* x, const double* y, const double* g1, const double* g2,
                          const double* w, int64_t n, double x0, double y0, double xmax, double ymax,
                          double delta, const Grid& g, void* scratch, void* gal_out,
-                         int32_t* cell_start, int64_t* m, hipStream_t s, int32_t* member = nullptr);
+                         int32_t* cell_start, int64_t* m, hipStream_t s, int32_t* member = nullptr,
+                         double* stats = nullptr);
 
 // stage (a) launcher, T = double or float: the pair-multipole kernel, then
 // the relayout of its records to centre-contiguous rows.  Returns the number

@@ -36,50 +36,11 @@
 //    binary64 masters every few batches (blocked summation).
 #include <type_traits>
 
-#include "fpcf4_internal.hpp"
+#include "stage_a_plan.hpp"
 
 namespace fpcf4 {
 namespace sa {
 
-enum { FA = 0, FB, FC, FD, FW, FE, FV, NF };
-
-// Order plan.  The plan index n is the record order nmax for the 4PCF; an
-// index 3PCF_PLAN + m selects the plan of the shear 3PCF on records of order
-// m: the same record layout, but only the orders the 3PCF reads are formed
-// (G up to 2m + 3, W up to 2m, and of the same-neighbour families Q up to 6,
-// A up to 2, V at 0: the blocks Q_-6, Q_-2, A_2, V_0 of its corrections),
-// and no triple-counting blocks.
-constexpr int PLAN3 = 100;
-__host__ __device__ constexpr bool is3(int n) { return n >= PLAN3; }
-__host__ __device__ constexpr int nord(int n) { return is3(n) ? n - PLAN3 : n; }
-// special units of pass 0: P8, Q8, P4, Q4, EA4, EB4 (complex); EA0, EB0, U (real)
-__host__ __device__ constexpr int nspecial(int n) { return is3(n) ? 0 : 15; }
-
-__host__ __device__ constexpr int kmax_f(int n, int f) {
-  return is3(n) ? ((f == FA || f == FB) ? 2 * nord(n) + 3
-                 : (f == FC || f == FD) ? 6
-                 : (f == FE)            ? 2
-                 : (f == FW)            ? 2 * nord(n)
-                                        : 0)
-                : ((f == FA || f == FB) ? 2 * n + 3
-                 : (f == FC || f == FD) ? imax(2 * n + 5, n + 6)
-                 : (f == FE)            ? imax(2 * n + 1, n + 2)
-                                        : 2 * n);
-}
-__host__ __device__ constexpr int ktop(int n) {
-  return is3(n) ? imax(2 * nord(n) + 3, 6) : imax(2 * n + 5, n + 6);
-}
-__host__ __device__ constexpr int units_at(int n, int k) {
-  int u = 0;
-  for (int f = 0; f < NF; ++f)
-    if (k <= kmax_f(n, f)) u += (k == 0 ? 1 : 2);
-  return u;
-}
-__host__ __device__ constexpr int total_units(int n) {
-  int u = nspecial(n);
-  for (int k = 0; k <= ktop(n); ++k) u += units_at(n, k);
-  return u;
-}
 // Split of the orders 0..ktop into passes of at most `cap` accumulator
 // units each (greedy, in order); pass 0 also holds the 15 special units
 // (orders 0, 4, 8 of the triple blocks, accumulated from z^4 and z^8 formed
@@ -178,25 +139,6 @@ __host__ __device__ constexpr int uidx(int n, int k0, int f, int k) {
 template <typename T> struct Budget;
 template <> struct Budget<float> { static constexpr int fold = 128; };
 template <> struct Budget<double> { static constexpr int fold = 1 << 30; };
-
-__device__ __forceinline__ double r2_exact(double dx, double dy) {
-#pragma clang fp contract(off)
-  const double a = dx * dx;
-  const double b = dy * dy;
-  return a + b;
-}
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ unsigned lane_id() { return __lane_id(); }
-
-__device__ __forceinline__ unsigned rank_in_mask(unsigned long long m) {
-  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-}
 
 template <typename T> __device__ __forceinline__ T rsq(T v);
 template <> __device__ __forceinline__ float rsq<float>(float v) { return __frsqrt_rn(v); }
@@ -607,7 +549,7 @@ __device__ __forceinline__ void pass_body(const StageAArgs& a,
           const int xcd = (xcd0 + xs) & 7;
           const int lo = (int)(((int64_t)a.ncent * xcd) >> 3);
           const int hi = (int)(((int64_t)a.ncent * (xcd + 1)) >> 3);
-          const int c = atomicAdd(a.work_counter + xcd, 1);
+          const int c = atomicAdd(a.work_counter + SCHED_STRIDE * xcd, 1);
           if (lo + c < hi) {
             idx = lo + c;
             break;
@@ -1092,6 +1034,10 @@ static hipError_t launch_pairs(const StageAArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The matrix-core kernel (stage_a_mfma.hip).
+template <int N, bool RED>
+hipError_t launch_pairs_mm(StageAArgs a, hipStream_t s);
+
 // The discrete bins (level 0) in one launch and, with the tree
 // approximation, the bins on reduced catalogues in a second one (its own
 // scheduling counters); then the relayout of all records.
@@ -1108,13 +1054,23 @@ hipError_t launch_n(const StageAArgs& a, hipStream_t s, int* nlaunch, hipEvent_t
   ae.b_hi = k;
   ar.b_lo = k;
   *nlaunch = 0;
-  hipError_t e = launch_pairs<T, N, false>(ae, s);
+  // binary32: on the matrix cores where the caller built octets (see
+  // matrix_scale in api.hip), else on the vector ALUs
+  const bool mm = a.octets[0] != nullptr;
+  bool mmr = true;
+  for (int b = k; b < a.b_hi; ++b) mmr = mmr && a.octets[a.level[b]] != nullptr;
+  constexpr bool matrix = sizeof(T) == 4 && use_matrix(N);
+  hipError_t e;
+  if constexpr (matrix) e = mm ? launch_pairs_mm<N, false>(ae, s) : launch_pairs<T, N, false>(ae, s);
+  else e = launch_pairs<T, N, false>(ae, s);
   if (e != hipSuccess) return e;
   *nlaunch = 1;
   if (red) {
     if constexpr (sizeof(T) == 4) {
-      ar.work_counter = a.work_counter + 8;
-      if ((e = launch_pairs<T, N, true>(ar, s)) != hipSuccess) return e;
+      ar.work_counter = a.work_counter + SCHED_WORDS;
+      if constexpr (matrix) e = mmr ? launch_pairs_mm<N, true>(ar, s) : launch_pairs<T, N, true>(ar, s);
+      else e = launch_pairs<T, N, true>(ar, s);
+      if (e != hipSuccess) return e;
       *nlaunch = 2;
     } else {
       return hipErrorInvalidValue;   // reduced catalogues: binary32 only

@@ -108,6 +108,10 @@ class LibBackend:
         from . import plan
         return plan(job.n, job.edges, job.nmax, job.precision, tile_centers=tile_centers)
 
+    def plan_smallest(self, job: Job, tile_centers: int):
+        from . import plan
+        return plan(job.n, job.edges, job.nmax, job.precision, tile_centers=tile_centers, smallest=True)
+
     def start(self, job: Job, tile_centers: int):
         from . import Request
         torch = self.torch
@@ -223,6 +227,9 @@ class Server:
             if nbytes <= self.budget or tile <= self.min_tile_centers:
                 break
             tile = max(self.min_tile_centers, tile // 2)
+        if nbytes > self.budget and hasattr(self.backend, "plan_smallest"):
+            # without the operand copies of the faster pair kernel
+            nbytes, ntiles = self.backend.plan_smallest(job, tile)
         if nbytes > self.budget:
             raise Fpcf4Error(E_BUDGET, f"request {job.rid} needs {nbytes} B, budget {self.budget} B")
         job.footprint, job.ntiles, job.tile_centers = int(nbytes), int(ntiles), tile
