@@ -20,11 +20,9 @@ hipError_t cells_build(const double*, const double*, const double*, const double
 hipError_t cells_centre_order(const uint32_t*, int64_t, const Grid&, uint32_t*, uint32_t*, int32_t*,
                               int32_t*, void*, size_t, hipStream_t);
 hipError_t cells_map_centres(const int64_t*, int64_t, const int32_t*, int32_t*, hipStream_t);
+size_t natural_tmp_bytes(int64_t ntrip, int nmax, int nphi);
 hipError_t natural_triplets(const double* ups, int nb, int nmax, int nphi, const int32_t* trip,
-                            int64_t ntrip, double* sel, double* tmp, double* binned, double* gamma,
-                            double* norm, hipStream_t s);
-hipError_t natural_components(const double* ups_dev, int nb, int nmax, int nphi, double* tmp,
-                              double* gamma_dev, double* norm_dev, hipStream_t s);
+                            int64_t ntrip, double* tmp, double* gamma, double* norm, hipStream_t s);
 }  // namespace fpcf4
 
 using namespace fpcf4;
@@ -1315,7 +1313,7 @@ fpcf4_status fpcf4_to_natural(const double* upsilon, int32_t nbins, int32_t nmax
   setup_pool();
   const int64_t nb3 = (int64_t)nbins * nbins * nbins, nn = 2 * nmax + 1;
   const size_t in_b = (size_t)(9 * nb3 * nn * nn) * 16;
-  const size_t tmp_b = (size_t)(9 * nb3 * nphi * nn) * 16;
+  const size_t tmp_b = natural_tmp_bytes(nb3, nmax, nphi);
   const size_t g_b = (size_t)(8 * nb3 * nphi * nphi) * 16;
   const size_t n_b = (size_t)(nb3 * nphi * nphi) * 8;
   char* buf = nullptr;
@@ -1326,7 +1324,7 @@ fpcf4_status fpcf4_to_natural(const double* upsilon, int32_t nbins, int32_t nmax
   double* dn = reinterpret_cast<double*>(buf + up(in_b) + up(tmp_b) + up(g_b));
   fpcf4_status st = FPCF4_OK;
   hipError_t e = hipMemcpyAsync(din, upsilon, in_b, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = natural_components(din, nbins, nmax, nphi, dtmp, dg, dn, s);
+  if (e == hipSuccess) e = natural_triplets(din, nbins, nmax, nphi, nullptr, nb3, dtmp, dg, dn, s);
   if (e == hipSuccess) e = hipMemcpyAsync(gamma_out, dg, g_b, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess && norm_out) e = hipMemcpyAsync(norm_out, dn, n_b, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1353,17 +1351,13 @@ fpcf4_status fpcf4_to_natural_triplets(const double* upsilon, int32_t ups_mem, i
   if (ntrip == 0) return FPCF4_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
   setup_pool();
-  const int64_t nn = 2 * nmax + 1;
   const size_t in_b = ups_mem == FPCF4_MEM_HOST ? (size_t)fpcf4_output_elems(nbins, nmax) * 16 : 0;
   const size_t trip_b = (size_t)ntrip * 3 * 4;
-  const size_t sel_b = (size_t)(9 * ntrip * nn * nn) * 16;
-  const size_t tmp_b = (size_t)(9 * ntrip * nphi * nn) * 16;
-  const size_t bin_b = (size_t)(9 * ntrip * nphi * nphi) * 16;
+  const size_t tmp_b = natural_tmp_bytes(ntrip, nmax, nphi);
   const size_t g_b = out_mem == FPCF4_MEM_HOST ? (size_t)(8 * ntrip * nphi * nphi) * 16 : 0;
   const size_t n_b = (size_t)(ntrip * nphi * nphi) * 8;   // always staged unless written in place
-  const size_t o_in = 0, o_trip = up(in_b), o_sel = o_trip + up(trip_b), o_tmp = o_sel + up(sel_b),
-               o_bin = o_tmp + up(tmp_b), o_g = o_bin + up(bin_b), o_n = o_g + up(g_b),
-               total = o_n + up(n_b);
+  const size_t o_in = 0, o_trip = up(in_b), o_tmp = o_trip + up(trip_b), o_g = o_tmp + up(tmp_b),
+               o_n = o_g + up(g_b), total = o_n + up(n_b);
   char* buf = nullptr;
   HIPCHK(hipMallocAsync(reinterpret_cast<void**>(&buf), total, s));
   const double* ups = ups_mem == FPCF4_MEM_HOST ? reinterpret_cast<const double*>(buf + o_in) : upsilon;
@@ -1376,8 +1370,7 @@ fpcf4_status fpcf4_to_natural_triplets(const double* upsilon, int32_t ups_mem, i
   if (e == hipSuccess) e = hipMemcpyAsync(buf + o_trip, triplets, trip_b, hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
     e = natural_triplets(ups, nbins, nmax, nphi, reinterpret_cast<const int32_t*>(buf + o_trip), ntrip,
-                         reinterpret_cast<double*>(buf + o_sel), reinterpret_cast<double*>(buf + o_tmp),
-                         reinterpret_cast<double*>(buf + o_bin), gdst, ndst, s);
+                         reinterpret_cast<double*>(buf + o_tmp), gdst, ndst, s);
   if (e == hipSuccess && !dev_out) {
     e = hipMemcpyAsync(gamma_out, gdst, g_b, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && norm_out) e = hipMemcpyAsync(norm_out, ndst, n_b, hipMemcpyDeviceToHost, s);
