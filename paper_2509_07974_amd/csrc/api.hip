@@ -91,6 +91,7 @@ struct PlanInfo {
   // create-time temporaries inside the region
   size_t t_raw, t_key_a, t_key_b, t_idx_a, t_idx_b, t_inv, t_sort, t_cent64;
   size_t base = 0;             // workspace without the octets
+  size_t o_upload, upload_bytes, o_zero, zero_bytes;   // host tables, buffers cleared at creation
   size_t o_octets[TREE_LEVELS_MAX + 1] = {};   // octets of the matrix-core pair kernel
   size_t total = 0;
 };
@@ -177,42 +178,48 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.o_gal = take(n * (P.precision == FPCF4_FP64 ? sizeof(Gal<double>) : sizeof(Gal<float>)));
   P.o_cells = take((P.ncell_cap + 1) * 4);
   P.o_centres = take((size_t)std::max<int64_t>(P.ncent, 1) * 4);
-  P.o_e2 = take((P.nb + 1) * 8);
-  P.o_edges = take((P.nb + 1) * 8);
   P.o_counters = take(kCounterWords * 4);   // scheduling counters, then the scaling maxima
-  P.o_bbox = take(kCatStats * 8);
-  P.o_bad = take(16);
-  P.o_pairs = take(16);
   P.ups_bytes = order == 4 ? (size_t)9 * P.nb * P.nb * P.nb * nn * nn * 16 : 0;
   P.corr_bytes = order == 4 ? corr_elems(P.nb, P.nmax) * 16 : 0;
   P.acc3_bytes = order == 3 ? three_elems(P.nb, m3) * 16 : 0;
-  P.o_ups = take(P.ups_bytes);
   const bool pairs = order == 4;
   if (pairs) {
-    const PairPlanHost pp = make_pair_plan(P.nmax, P.nb);
+    const PairPlanHost& pp = pair_plan(P.nmax);
     for (const PairOut& o : pp.out)
       if (o.item < 0 || o.item >= (int32_t)pp.items.size())
         return fail(FPCF4_E_DEVICE, "internal: contraction plan leaves an output unassigned");
     P.pitems = (int64_t)pp.items.size();
-    P.prows = pp.total_rows;
+    P.prows = pp.total_rows * P.nb;
     const size_t slice_bytes = (size_t)P.prows * P.nb * P.nb * 8;
     const int64_t fit = std::max<int64_t>(1, (int64_t)(kPairPartialBudget / std::max<size_t>(slice_bytes, 1)));
     P.pslices = (int)std::min<int64_t>(pair_slices(P.tile), fit);
   }
-  P.o_pitems = take((size_t)P.pitems * sizeof(PairItem));
-  P.o_pout = take(pairs ? (size_t)FPCF4_NCORR * nn * nn * sizeof(PairOut) : 0);
-  P.o_ppart = take((size_t)P.pslices * P.prows * P.nb * P.nb * 8);
-  P.o_corr = take(P.corr_bytes);
-  P.o_cpart = take(P.corr_bytes * CORR_SLICES);
   if (pairs) {
-    const CorrPlanHost cp = make_corr_plan(P.nmax);
+    const CorrPlanHost& cp = corr_plan(P.nmax);
     P.csums = (int)cp.sums.size();
     P.cpair = cp.npair;
     P.cmap = (int)cp.map.size();
   }
+  // host tables, uploaded in one copy
+  P.o_upload = off;
+  P.o_e2 = take((P.nb + 1) * 8);
+  P.o_edges = take((P.nb + 1) * 8);
+  P.o_pitems = take((size_t)P.pitems * sizeof(PairItem));
+  P.o_pout = take(pairs ? (size_t)FPCF4_NCORR * nn * nn * sizeof(PairOut) : 0);
   P.o_csums = take((size_t)P.csums * sizeof(CorrSum));
   P.o_cmap = take((size_t)P.cmap * 4);
+  P.upload_bytes = off - P.o_upload;
+  // buffers cleared together
+  P.o_zero = off;
+  P.o_bbox = take(kCatStats * 8 + 16);
+  P.o_bad = P.o_bbox + kCatStats * 8;   // read back with the statistics
+  P.o_pairs = take(16);
+  P.o_corr = take(P.corr_bytes);
   P.o_acc3 = take(P.acc3_bytes);
+  P.o_ups = take(P.ups_bytes);
+  P.zero_bytes = off - P.o_zero;
+  P.o_ppart = take((size_t)P.pslices * P.prows * P.nb * P.nb * 8);
+  P.o_cpart = take(P.corr_bytes * CORR_SLICES);
   P.o_part3 = take(P.acc3_bytes * THREE_SLICES);
   for (int d = 1; d <= P.tree_levels; ++d) {
     P.o_rgal[d - 1] = take(n * sizeof(GalR<float>));
@@ -287,8 +294,8 @@ struct fpcf4_request {
   bool mm[TREE_LEVELS_MAX + 1] = {};        // octets built for the galaxies / reduced catalogue d
   MatScale ms[TREE_LEVELS_MAX + 1] = {};
   std::vector<char> stepped;
-  PairPlanHost pplan;           // the contraction plan uploaded into the workspace (4PCF)
-  CorrPlanHost cplan;           // the distinct degenerate-term sums, likewise
+  const PairPlanHost* pplan = nullptr;   // the contraction plan uploaded into the workspace (4PCF)
+  std::vector<char> upload;              // the tables as uploaded, until the copy has completed
   bool want_counts = false;
   bool no_events = false;       // allocation-free path: never create profiling events
   std::vector<hipEvent_t> ev;   // 4 per profiled step
@@ -351,6 +358,8 @@ bool matrix_scale_reduced(const double* st, int64_t m, MatScale& s) {
   return true;
 }
 
+constexpr int64_t kPackedCopyMax = 8192;
+
 fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
                           const fpcf4_options* opts, void* wsp, size_t bytes, fpcf4_request* R,
                           int order = 4, int m3 = 0, const fpcf4_tree* tree = nullptr) {
@@ -382,32 +391,29 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
       if (hc[k] < 0 || hc[k] >= n) return fail(FPCF4_E_INVALID_ARG, "centre index %lld out of range", (long long)hc[k]);
   }
 
+  R->upload.assign(P.upload_bytes, 0);
+  auto table = [&](size_t off) { return R->upload.data() + (off - P.o_upload); };
+  double* e2 = reinterpret_cast<double*>(table(P.o_e2));
+  for (int b = 0; b <= P.nb; ++b) e2[b] = bins->edges[b] * bins->edges[b];
+  std::memcpy(table(P.o_edges), bins->edges, (P.nb + 1) * 8);
   if (P.pitems > 0) {
-    R->pplan = make_pair_plan(P.nmax, P.nb);
-    HIPCHK(hipMemcpyAsync(R->ws + P.o_pitems, R->pplan.items.data(), R->pplan.items.size() * sizeof(PairItem),
-                          hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(R->ws + P.o_pout, R->pplan.out.data(), R->pplan.out.size() * sizeof(PairOut),
-                          hipMemcpyHostToDevice, s));
+    R->pplan = &pair_plan(P.nmax);
+    PairItem* items = reinterpret_cast<PairItem*>(table(P.o_pitems));
+    for (size_t k = 0; k < R->pplan->items.size(); ++k) {
+      items[k] = R->pplan->items[k];
+      items[k].row0 *= P.nb;
+    }
+    std::memcpy(table(P.o_pout), R->pplan->out.data(), R->pplan->out.size() * sizeof(PairOut));
   }
   if (P.csums > 0) {
-    R->cplan = make_corr_plan(P.nmax);
-    for (int32_t v : R->cplan.map)
+    const CorrPlanHost& cp = corr_plan(P.nmax);
+    for (int32_t v : cp.map)
       if (v < 0 || v >= P.csums) return fail(FPCF4_E_DEVICE, "internal: correction plan leaves a sum unassigned");
-    HIPCHK(hipMemcpyAsync(R->ws + P.o_csums, R->cplan.sums.data(), R->cplan.sums.size() * sizeof(CorrSum),
-                          hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(R->ws + P.o_cmap, R->cplan.map.data(), R->cplan.map.size() * 4, hipMemcpyHostToDevice,
-                          s));
+    std::memcpy(table(P.o_csums), cp.sums.data(), cp.sums.size() * sizeof(CorrSum));
+    std::memcpy(table(P.o_cmap), cp.map.data(), cp.map.size() * 4);
   }
-  HIPCHK(hipMemsetAsync(R->ws + P.o_pairs, 0, 16, s));
-  if (P.ups_bytes) HIPCHK(hipMemsetAsync(R->ws + P.o_ups, 0, P.ups_bytes, s));
-  if (P.corr_bytes) HIPCHK(hipMemsetAsync(R->ws + P.o_corr, 0, P.corr_bytes, s));
-  if (P.acc3_bytes) HIPCHK(hipMemsetAsync(R->ws + P.o_acc3, 0, P.acc3_bytes, s));
-  double e2[FPCF4_NBINS_SUPPORTED + 1];
-  for (int b = 0; b <= P.nb; ++b) e2[b] = bins->edges[b] * bins->edges[b];
-  HIPCHK(hipMemcpyAsync(R->ws + P.o_e2, e2, (P.nb + 1) * 8, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(R->ws + P.o_edges, bins->edges, (P.nb + 1) * 8, hipMemcpyHostToDevice, s));
-  // the copy from the stack array must complete before it goes out of scope
-  HIPCHK(hipStreamSynchronize(s));
+  HIPCHK(hipMemcpyAsync(R->ws + P.o_upload, R->upload.data(), P.upload_bytes, hipMemcpyHostToDevice, s));
+  HIPCHK(hipMemsetAsync(R->ws + P.o_zero, 0, P.zero_bytes, s));
   if (n == 0) {
     HIPCHK(hipStreamSynchronize(s));
     return FPCF4_OK;
@@ -415,24 +421,31 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
 
   char* reg = R->ws + P.o_region;
   const double *x, *y, *g1, *g2, *w;
+  std::vector<double> packed;
   if (cat->mem == FPCF4_MEM_HOST) {
     double* raw = reinterpret_cast<double*>(reg + P.t_raw);
     const double* src[5] = {cat->x, cat->y, cat->g1, cat->g2, cat->w};
-    for (int k = 0; k < 5; ++k)
-      HIPCHK(hipMemcpyAsync(raw + k * n, src[k], n * 8, hipMemcpyHostToDevice, s));
+    if (n <= kPackedCopyMax) {
+      // one copy: a copy from pageable memory costs some 10 us whatever its size
+      packed.resize((size_t)n * 5);
+      for (int k = 0; k < 5; ++k) std::memcpy(packed.data() + k * n, src[k], n * 8);
+      HIPCHK(hipMemcpyAsync(raw, packed.data(), n * 40, hipMemcpyHostToDevice, s));
+    } else {
+      for (int k = 0; k < 5; ++k) HIPCHK(hipMemcpyAsync(raw + k * n, src[k], n * 8, hipMemcpyHostToDevice, s));
+    }
     x = raw; y = raw + n; g1 = raw + 2 * n; g2 = raw + 3 * n; w = raw + 4 * n;
   } else {
     x = cat->x; y = cat->y; g1 = cat->g1; g2 = cat->g2; w = cat->w;
   }
   unsigned* bad = R->at<unsigned>(P.o_bad);
-  HIPCHK(hipMemsetAsync(bad, 0, 16, s));
   HIPCHK(cells_stats(x, y, g1, g2, w, n, reinterpret_cast<double*>(reg + P.t_key_a), bad,
                      R->at<double>(P.o_bbox), s));
-  double bb[kCatStats];
-  unsigned hbad = 0;
+  double bb[kCatStats + 1];
   HIPCHK(hipMemcpyAsync(bb, R->ws + P.o_bbox, sizeof bb, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  R->upload = std::vector<char>();
+  unsigned hbad;
+  std::memcpy(&hbad, bb + kCatStats, 4);
   if (hbad) return fail(FPCF4_E_INVALID_ARG, "catalogue has %u non-finite entries", hbad);
 
   // cell grid: side ~ outer edge / 48 (<= ~99 cell rows per annulus, two row
@@ -587,8 +600,8 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
     pl.items = R->at<PairItem>(P.o_pitems);
     pl.out = R->at<PairOut>(P.o_pout);
     for (int c = 0; c <= PAIR_MAX_BLK; ++c) {
-      pl.cls_start[c] = R->pplan.cls_start[c];
-      pl.cls_count[c] = R->pplan.cls_count[c];
+      pl.cls_start[c] = R->pplan->cls_start[c];
+      pl.cls_count[c] = R->pplan->cls_count[c];
     }
     pl.ncent = ncent;
     pl.nb = P.nb;
@@ -607,11 +620,11 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
     else HIPCHK(launch_corrections<float>(ca, s));
     if (prof) {
       HIPCHK(hipEventRecord(evs[4], s));
-      R->prof_b_flops += pair_issued_flops(R->pplan, P.nb, ncent, P.precision);
-      R->prof_b_useful += pair_useful_flops(R->pplan, P.nb, ncent);
+      R->prof_b_flops += pair_issued_flops(*R->pplan, P.nb, ncent, P.precision);
+      R->prof_b_useful += pair_useful_flops(*R->pplan, P.nb, ncent);
       R->prof_a_launches += nlaunch;
       // one kernel per row-block class, the slice sum (several slices), the scatter
-      R->prof_b_launches += (R->pplan.cls_count[1] > 0) + (R->pplan.cls_count[2] > 0) +
+      R->prof_b_launches += (R->pplan->cls_count[1] > 0) + (R->pplan->cls_count[2] > 0) +
                             (std::min(pair_slices(ncent), P.pslices) > 1) + 1;
       R->prof_steps += 1;
       R->prof_centres += ncent;
@@ -1131,7 +1144,7 @@ fpcf4_status fpcf4_debug_pair_plan(int32_t nmax, int32_t* out, int64_t* nitems) 
   if (nmax < 0 || nmax > FPCF4_NMAX_SUPPORTED) return fail(FPCF4_E_INVALID_ARG, "nmax %d outside [0, %d]", nmax,
                                                           FPCF4_NMAX_SUPPORTED);
   if (!out) return fail(FPCF4_E_INVALID_ARG, "null out");
-  const PairPlanHost pp = make_pair_plan(nmax, 1);
+  const PairPlanHost& pp = pair_plan(nmax);
   for (size_t o = 0; o < pp.out.size(); ++o) {
     const PairOut& po = pp.out[o];
     int32_t* v = out + 16 * o;
@@ -1151,7 +1164,7 @@ fpcf4_status fpcf4_debug_corr_plan(int32_t nmax, int32_t* out, int64_t* nsums) {
   if (nmax < 0 || nmax > FPCF4_NMAX_SUPPORTED) return fail(FPCF4_E_INVALID_ARG, "nmax %d outside [0, %d]", nmax,
                                                           FPCF4_NMAX_SUPPORTED);
   if (!out) return fail(FPCF4_E_INVALID_ARG, "null out");
-  const CorrPlanHost cp = make_corr_plan(nmax);
+  const CorrPlanHost& cp = corr_plan(nmax);
   const Layout L = make_layout(nmax);
   // record entry -> (family code, signed order) of the block it holds
   auto block_of = [&](int e, int flip, int& fam, int& ord) {

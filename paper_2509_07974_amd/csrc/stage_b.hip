@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <array>
 #include <map>
+#include <mutex>
 
 #include "factors.hpp"
 #include "fpcf4_internal.hpp"
@@ -95,6 +96,12 @@ CorrPlanHost make_corr_plan(int n) {
   P.sums = pairs;
   P.sums.insert(P.sums.end(), triples.begin(), triples.end());
   return P;
+}
+const CorrPlanHost& corr_plan(int nmax) {
+  static std::once_flag once[FPCF4_NMAX_SUPPORTED + 1];
+  static CorrPlanHost plan[FPCF4_NMAX_SUPPORTED + 1];
+  std::call_once(once[nmax], [nmax] { plan[nmax] = make_corr_plan(nmax); });
+  return plan[nmax];
 }
 
 typedef double d4 __attribute__((ext_vector_type(4)));

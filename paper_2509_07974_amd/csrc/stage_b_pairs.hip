@@ -48,6 +48,7 @@
 #include <algorithm>
 #include <array>
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <type_traits>
 #include <vector>
@@ -892,6 +893,13 @@ static void launch_f64_nbc(const PairArgs& a, int nblk, int nsl, hipStream_t s) 
     hipLaunchKernelGGL((contract_pair_f64_kernel<1, NBC>), grid, dim3(64 * pair_waves(1, NBC)), 0, s, a);
   else
     hipLaunchKernelGGL((contract_pair_f64_kernel<2, NBC>), grid, dim3(64 * pair_waves(2, NBC)), 0, s, a);
+}
+
+const PairPlanHost& pair_plan(int nmax) {
+  static std::once_flag once[FPCF4_NMAX_SUPPORTED + 1];
+  static PairPlanHost plan[FPCF4_NMAX_SUPPORTED + 1];
+  std::call_once(once[nmax], [nmax] { plan[nmax] = make_pair_plan(nmax, 1); });
+  return plan[nmax];
 }
 
 double pair_issued_flops(const PairPlanHost& pp, int nb, int64_t ncent, int precision) {
