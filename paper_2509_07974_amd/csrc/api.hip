@@ -1,5 +1,6 @@
 // Host side of the C ABI: validation, planning, workspace layout and the
 // request life cycle (create -> step per centre tile -> finalize).
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -76,9 +77,9 @@ struct PlanInfo {
   // persistent buffers
   size_t o_gal, o_cells, o_centres, o_e2, o_edges, o_counters, o_bbox, o_bad,
       o_pairs, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
-      o_aos, o_region, o_pitems, o_pout, o_ppart, o_csums, o_cmap;
+      o_aos, o_region, o_pitems, o_pout, o_ppart, o_ppart_fill, o_csums, o_cmap;
   // contraction work items (each distinct product of three blocks once)
-  int pslices = 0;
+  int pslices = 0, pslices_fill = 0;   // of the contraction: in a workspace of `base` bytes, of `total` bytes
   int64_t pitems = 0, prows = 0;
   // distinct degenerate-term sums
   int csums = 0, cpair = 0, cmap = 0;
@@ -191,8 +192,10 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     P.pitems = (int64_t)pp.items.size();
     P.prows = pp.total_rows * P.nb;
     const size_t slice_bytes = (size_t)P.prows * P.nb * P.nb * 8;
-    const int64_t fit = std::max<int64_t>(1, (int64_t)(kPairPartialBudget / std::max<size_t>(slice_bytes, 1)));
-    P.pslices = (int)std::min<int64_t>(pair_slices(P.tile), fit);
+    const int64_t fit = std::clamp<int64_t>((int64_t)(kPairPartialBudget / std::max<size_t>(slice_bytes, 1)), 1,
+                                            PAIR_SLICES_MAX);
+    P.pslices = pair_slices(P.tile, pp, P.nb, false, fit);
+    P.pslices_fill = pair_slices(P.tile, pp, P.nb, true, fit);
   }
   if (pairs) {
     const CorrPlanHost& cp = corr_plan(P.nmax);
@@ -248,6 +251,9 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   // a workspace without room for them still serves with the vector kernel
   if (P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax))
     for (int d = 0; d <= P.tree_levels; ++d) P.o_octets[d] = take(octet_bytes(n));
+  // likewise the partials of the contraction's extra slices
+  P.o_ppart_fill = P.o_ppart;
+  if (P.pslices_fill > P.pslices) P.o_ppart_fill = take((size_t)P.pslices_fill * P.prows * P.nb * P.nb * 8);
   P.total = off;
   return FPCF4_OK;
 }
@@ -296,6 +302,7 @@ struct fpcf4_request {
   std::vector<char> stepped;
   const PairPlanHost* pplan = nullptr;   // the contraction plan uploaded into the workspace (4PCF)
   std::vector<char> upload;              // the tables as uploaded, until the copy has completed
+  bool full = false;            // the workspace has the `total` bytes, not only the `base`
   bool want_counts = false;
   bool no_events = false;       // allocation-free path: never create profiling events
   std::vector<hipEvent_t> ev;   // 4 per profiled step
@@ -369,7 +376,8 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   if (!wsp) return fail(FPCF4_E_INVALID_ARG, "null workspace");
   if (reinterpret_cast<uintptr_t>(wsp) % ALIGN) return fail(FPCF4_E_INVALID_ARG, "workspace not 256-byte aligned");
   if (bytes < P.base) return fail(FPCF4_E_BUDGET, "workspace %zu bytes < planned %zu", bytes, P.base);
-  const bool octets = P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax) && bytes >= P.total;
+  R->full = bytes >= P.total;
+  const bool octets = P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax) && R->full;
   R->edges.assign(bins->edges, bins->edges + P.nb + 1);
   R->ws = static_cast<char*>(wsp);
   R->stream = static_cast<hipStream_t>(opts->stream);
@@ -607,8 +615,8 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
     pl.nb = P.nb;
     pl.nmax = P.nmax;
     pl.precision = P.precision;
-    pl.max_slices = P.pslices;
-    pl.part = R->at<double>(P.o_ppart);
+    pl.nslices = pair_slices(ncent, *R->pplan, P.nb, R->full, R->full ? P.pslices_fill : P.pslices);
+    pl.part = R->at<double>(R->full ? P.o_ppart_fill : P.o_ppart);
     pl.total_rows = P.prows;
     pl.ups = R->at<double>(P.o_ups);
     HIPCHK(launch_contract_pairs(pl, s));
@@ -625,7 +633,7 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
       R->prof_a_launches += nlaunch;
       // one kernel per row-block class, the slice sum (several slices), the scatter
       R->prof_b_launches += (R->pplan->cls_count[1] > 0) + (R->pplan->cls_count[2] > 0) +
-                            (std::min(pair_slices(ncent), P.pslices) > 1) + 1;
+                            (pl.nslices > 1) + 1;
       R->prof_steps += 1;
       R->prof_centres += ncent;
     }

@@ -301,7 +301,9 @@ PairPlanHost make_pair_plan(int nmax, int nb);
 // make_pair_plan(nmax, 1), kept likewise: row0 and total_rows scale with nb.
 // Making it takes 0.5 ms at nmax 3 and 9 ms at nmax 15.
 const PairPlanHost& pair_plan(int nmax);
-int pair_slices(int64_t ncent);    // centre slices (partial regions) for a tile
+// centre slices (partial regions) for a tile, at most `cap`; with `fill`, as many as fill the chip
+constexpr int PAIR_SLICES_MAX = 32;
+int pair_slices(int64_t ncent, const PairPlanHost& pp, int nb, bool fill, int64_t cap);
 struct PairArgs {
   const void* rec;                 // records (binary32 or binary64 complex)
   int64_t ldc;
@@ -324,7 +326,7 @@ struct PairLaunch {
   const PairOut* out;
   int cls_start[PAIR_MAX_BLK + 1], cls_count[PAIR_MAX_BLK + 1];
   int ncent, nb, nmax, precision;
-  int max_slices;                  // centre slices the partial buffer holds
+  int nslices;                     // centre slices, at most what the partial buffer holds
   double* part;
   int64_t total_rows;
   double* ups;                     // accumulated into

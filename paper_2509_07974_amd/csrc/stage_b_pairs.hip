@@ -224,11 +224,30 @@ PairPlanHost make_pair_plan(int nmax, int nb) {
   return P;
 }
 
-// centre slices of the pair contraction: enough workgroups to fill the chip,
-// at most 32 (each slice owns a binary64 partial region of every item)
-int pair_slices(int64_t ncent) {
+constexpr int PKC = 32;             // centres per staged chunk (two K-steps of 16)
+
+// Centre slices of the pair contraction, at most `cap` (each owns a binary64
+// partial region of every item) and none of them empty.  Slices of PAIR_SUB
+// centres for large tiles; with `fill`, as many more as a small tile needs for
+// PAIR_FILL workgroups in a launch, of at least PAIR_SLICE_MIN centres: 2000
+// centres at nmax 3 have 74 work items, and one slice of them left most of the
+// chip idle (binary64 480 us, fp16 203; with 15 slices 70 and 27, and 5 more to
+// add them).  Where the items fill it nothing is gained: 30011 centres at nmax
+// 8 3.16 ms with 4 slices as with 6.
+constexpr int PAIR_FILL = 2048;       // 8 workgroups per CU, two rounds of those resident
+constexpr int PAIR_SLICE_MIN = 128;
+int pair_slices(int64_t ncent, const PairPlanHost& pp, int nb, bool fill, int64_t cap) {
   int64_t s = (ncent + PAIR_SUB - 1) / PAIR_SUB;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(s, 32));
+  if (fill) {
+    const BinTiles bt = bin_tiles(nb);
+    int64_t groups = 1;
+    for (int k = 1; k <= PAIR_MAX_BLK; ++k) groups = std::max<int64_t>(groups, pp.cls_count[k]);
+    groups *= (int64_t)bt.nt * bt.nt * bt.nt;
+    s = std::max(s, std::min((PAIR_FILL + groups - 1) / groups, ncent / PAIR_SLICE_MIN));
+  }
+  s = std::max<int64_t>(1, std::min(s, cap));
+  const int64_t per = std::max<int64_t>(1, (((ncent + s - 1) / s) + PKC - 1) / PKC) * PKC;   // as the kernels cut them
+  return (int)std::max<int64_t>(1, (ncent + per - 1) / per);
 }
 
 // ---------------------------------------------------------------------------
@@ -248,7 +267,6 @@ struct cf {
   float r, i;
 };
 
-constexpr int PKC = 32;             // centres per staged chunk (two K-steps of 16)
 constexpr int PKS = PKC / 16;
 
 // row tiles, column tiles, waves and column tiles per wave for NBLK row
@@ -923,7 +941,7 @@ double pair_useful_flops(const PairPlanHost& pp, int nb, int64_t ncent) {
 
 hipError_t launch_contract_pairs(const PairLaunch& pl, hipStream_t s) {
   if (pl.ncent <= 0) return hipSuccess;
-  const int nsl = std::min(pair_slices(pl.ncent), std::max(1, pl.max_slices));
+  const int nsl = std::max(1, pl.nslices);
   const BinTiles bt = bin_tiles(pl.nb);
   for (int nblk = 1; nblk <= PAIR_MAX_BLK; ++nblk) {
     if (pl.cls_count[nblk] == 0) continue;
