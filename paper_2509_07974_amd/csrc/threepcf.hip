@@ -26,11 +26,12 @@
 // W_k for |k| <= 2 n4, Q_-6, Q_-2, A_2 and V_0, so 3PCF multipoles up to
 // |n| <= 2 n4 are read from it directly.
 //
-// The contraction is tiny next to stage (a) (5 (2m+1) nb^2 complex products
-// per centre): one workgroup per (n, mu, centre slice), the slot values of a
-// chunk of centres staged in LDS, one output (b1, b2) per thread, binary64
-// throughout (the records are converted on load).  Each slice writes its own
-// partial buffer; the slices are added in slice order (deterministic).
+// The contraction (5 (2m+1) nb^2 complex products per centre) is binary64
+// throughout (the records are converted on load).  A wave takes a tile of T1 x
+// T2 outputs (b1, b2) of one (n, mu, centre slice), a lane every 64th centre
+// of the slice: T1 + T2 loads feed T1 T2 products, all in registers, and the
+// lanes' sums are added at the end.  Each slice writes its own partial buffer;
+// the slices are added in slice order (deterministic).
 #include "fpcf4_internal.hpp"
 
 namespace fpcf4 {
@@ -56,7 +57,7 @@ __host__ __device__ constexpr Row3 row3(int mu) {
                  : Row3{2, {true, false, 1, 0}, {true, false, -1, 0}, 2, 0, false};
 }
 
-constexpr int CH3 = 32;   // centres per LDS chunk
+constexpr int CH3 = 64;   // centres of a slice, a multiple of the wave
 
 __device__ inline int slot_entry(const Layout& L, const Slot3& f, int n) {
   const int k = f.s * n + f.o;
@@ -82,78 +83,113 @@ __host__ __device__ inline int slice_len(int ncent, int parts) {
   return (per + CH3 - 1) / CH3 * CH3;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void contract3_kernel(ThreeArgs a) {
-  // blockIdx.x = ni nt1 nt2 + bin tile (t1, t2): b1 in [o1, o1 + n1), b2 in
-  // [o2, o2 + n2), inside the slot ranges [lo1, lo1 + nb1) and [lo2, lo2 + nb2)
-  const BinTiles bt1 = bin_tiles(a.nb1), bt2 = bin_tiles(a.nb2);
-  const int ntt = bt1.nt * bt2.nt;
-  const int ni = (int)blockIdx.x / ntt;
-  const int t12 = (int)blockIdx.x % ntt;
-  const int o1 = a.lo1 + (t12 / bt2.nt) * bt1.tb, o2 = a.lo2 + (t12 % bt2.nt) * bt2.tb;
-  const int n1 = min(bt1.tb, a.lo1 + a.nb1 - o1), n2 = min(bt2.tb, a.lo2 + a.nb2 - o2);
-  const int mu = blockIdx.y;
-  const int sl = blockIdx.z;
-  const int n = ni - a.m;
-  const int nb = a.nb;
+// Bin tiles of a dimension: as many of t bins as cover nb.
+__host__ __device__ inline int tiles3(int nb, int t) { return (nb + t - 1) / t; }
+
+// Lane l ends with the sum over the lanes of value l of v[0, 64): lanes that
+// differ in bit W exchange halves of the values (indexes known at compile time,
+// so that they stay in registers).
+template <int W>
+__device__ __forceinline__ void transpose_sum(double (&v)[64], int lane) {
+  const bool up = (lane & W) != 0;
+#pragma unroll
+  for (int k = 0; k < W; ++k) {
+    const double keep = up ? v[k + W] : v[k], send = up ? v[k] : v[k + W];
+    v[k] = keep + __shfl_xor(send, W, 64);
+  }
+  if constexpr (W > 1) transpose_sum<W / 2>(v, lane);
+}
+
+// One wave per (n, mu, slice, tile); blockIdx.x = n times the workgroups of
+// four consecutive tiles, which share slot-1 records through L1.  Bound by the
+// binary64 multiply-adds, four per product (and per 64 centres of a tile 6 T1 +
+// 3 T2 + 12 more for conversions and the centre factor), and in binary64 by
+// the records' way from L2 (T1 + T2 of 16 bytes per centre and tile).  27000
+// galaxies, 65 bins, |n| <= 15, binary64: 6.6 ms; the three tree levels' sums of
+// 1e6 galaxies, 12 bins, |n| <= 10: 13 ms.  One output per thread with the
+// records staged in LDS read 32 bytes of LDS for every four multiply-adds and
+// took 9.0 and 42 ms.
+static_assert(THREE_SLICES % 8 == 0, "equal shares for the XCDs");
+template <typename T, int T1, int T2>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void contract3_kernel(ThreeArgs a) {
+  static_assert(2 * T1 * T2 <= 64, "one lane per component of the tile's sums");
+  const int nt2 = tiles3(a.nb2, T2), ntt = tiles3(a.nb1, T1) * nt2, groups = (ntt + 3) / 4;
+  // workgroups are dealt to the 8 XCDs round-robin: give each XCD a contiguous
+  // range of (slice, mu, n, tile), so that the tiles of one (n, mu, slice) read
+  // its records through one L2
+  const unsigned all = gridDim.x * 5u * THREE_SLICES;
+  const unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + 5u * blockIdx.z);
+  const unsigned id = (lin & 7u) * (all / 8u) + (lin >> 3);
+  const int bx = (int)(id % gridDim.x), mu = (int)(id / gridDim.x % 5u), sl = (int)(id / gridDim.x / 5u);
+  const int ni = bx / groups;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int tile = (bx - ni * groups) * 4 + wv;
+  if (tile >= ntt) return;
+  const int lane = (int)(threadIdx.x & 63);
+  const int u1 = tile / nt2 * T1, u2 = (tile - tile / nt2 * nt2) * T2;   // first bins of the tile in the slot ranges
+  const int n = ni - a.m, nb = a.nb;
   const Layout L = make_layout(a.n4);
   const Row3 r = row3(mu);
-  const int e1 = slot_entry(L, r.f1, n), e2 = slot_entry(L, r.f2, n);
   const int per = slice_len(a.ncent, THREE_SLICES);
-  const int c0 = sl * per;
-  const int c1 = min(a.ncent, c0 + per);
-  __shared__ double2 Ls[BIN_TILE_MAX][CH3 + 1];
-  __shared__ double2 Rs[BIN_TILE_MAX][CH3 + 1];
-  const int t = threadIdx.x;
-  const bool owner = t < n1 * n2;
-  const int b1 = owner ? t / n2 : 0, b2 = owner ? t % n2 : 0;
-  const T* rec = static_cast<const T*>(a.rec);
-  double ar = 0.0, ai = 0.0;
-  for (int cb = c0; cb < c1; cb += CH3) {
-    for (int q = t; q < (n1 + n2) * CH3; q += blockDim.x) {
-      const int side = q >= n1 * CH3;
-      const int rem = side ? q - n1 * CH3 : q;
-      const int b = rem / CH3, c = rem - (rem / CH3) * CH3;
-      const int ci = cb + c;
-      double vr = 0.0, vi = 0.0;
-      if (ci < c1) {
-        const int32_t* par = side ? a.par2 : a.par1;
-        const int col = par ? par[ci] : ci;
-        const T* rs = side ? static_cast<const T*>(a.rec2) : rec;
-        const size_t o = (((size_t)(side ? e2 : e1) * nb + (side ? o2 : o1) + b) * (side ? a.ldc2 : a.ldc) + col) * 2;
-        vr = (double)rs[o];
-        vi = (double)rs[o + 1];
-        if (side ? r.f2.conj : r.f1.conj) vi = -vi;
-        if (!side) {
-          double xr, xi;
-          centre_factor<T>(a, r.x, ci, xr, xi);
-          const double tr = xr * vr - xi * vi;
-          vi = xr * vi + xi * vr;
-          vr = tr;
-        }
-      }
-      if (side) Rs[b][c] = make_double2(vr, vi);
-      else Ls[b][c] = make_double2(vr, vi);
+  const int c0 = sl * per, c1 = min(a.ncent, c0 + per);
+  // records of the tile's bins (past the range: the last bin again, not stored)
+  const T* r1 = static_cast<const T*>(a.rec) + 2 * ((size_t)slot_entry(L, r.f1, n) * nb + a.lo1) * a.ldc;
+  const T* r2 = static_cast<const T*>(a.rec2) + 2 * ((size_t)slot_entry(L, r.f2, n) * nb + a.lo2) * a.ldc2;
+  const T* p1[T1];
+  const T* p2[T2];
+#pragma unroll
+  for (int b = 0; b < T1; ++b) p1[b] = r1 + 2 * (size_t)min(u1 + b, a.nb1 - 1) * a.ldc;
+#pragma unroll
+  for (int b = 0; b < T2; ++b) p2[b] = r2 + 2 * (size_t)min(u2 + b, a.nb2 - 1) * a.ldc2;
+  const double s1 = r.f1.conj ? -1.0 : 1.0;
+  const T s2 = r.f2.conj ? T(-1) : T(1);
+  double v[64];
+#pragma unroll
+  for (int k = 0; k < 64; ++k) v[k] = 0.0;
+  for (int cb = c0; cb < c1; cb += 64) {
+    const int ci = min(cb + lane, c1 - 1);
+    const int col1 = a.par1 ? a.par1[ci] : ci, col2 = a.par2 ? a.par2[ci] : ci;
+    T f1[T1][2], f2[T2][2];
+#pragma unroll
+    for (int b = 0; b < T1; ++b) {
+      f1[b][0] = p1[b][2 * (size_t)col1];
+      f1[b][1] = p1[b][2 * (size_t)col1 + 1];
     }
-    __syncthreads();
-    if (owner) {
-#pragma unroll 8
-      for (int c = 0; c < CH3; ++c) {
-        const double2 l = Ls[b1][c], q = Rs[b2][c];
-        ar = fma(l.x, q.x, ar);
-        ar = fma(-l.y, q.y, ar);
-        ai = fma(l.x, q.y, ai);
-        ai = fma(l.y, q.x, ai);
+#pragma unroll
+    for (int b = 0; b < T2; ++b) {
+      f2[b][0] = p2[b][2 * (size_t)col2];
+      f2[b][1] = p2[b][2 * (size_t)col2 + 1];
+    }
+    double xr, xi;
+    centre_factor<T>(a, r.x, ci, xr, xi);
+    if (cb + lane >= c1) xr = xi = 0.0;
+    const double yr = s1 * xr, yi = s1 * xi;
+    double gr[T2], gi[T2];
+#pragma unroll
+    for (int b = 0; b < T2; ++b) {
+      gr[b] = (double)f2[b][0];
+      gi[b] = (double)(s2 * f2[b][1]);
+    }
+#pragma unroll
+    for (int b = 0; b < T1; ++b) {
+      const double fr = (double)f1[b][0], fi = (double)f1[b][1];
+      const double lr = fma(xr, fr, -(yi * fi)), li = fma(xi, fr, yr * fi);
+#pragma unroll
+      for (int q = 0; q < T2; ++q) {
+        double& ar = v[2 * (b * T2 + q)];
+        double& ai = v[2 * (b * T2 + q) + 1];
+        ar = fma(lr, gr[q], ar);
+        ai = fma(lr, gi[q], ai);
+        ar = fma(-li, gi[q], ar);
+        ai = fma(li, gr[q], ai);
       }
     }
-    __syncthreads();
   }
-  if (owner) {
-    double* p = a.part + 2 * ((size_t)sl * three_elems(nb, a.m) + ((size_t)mu * a.nn + ni) * nb * nb +
-                              (size_t)(o1 + b1) * nb + o2 + b2);
-    p[0] = ar;
-    p[1] = ai;
-  }
+  transpose_sum<32>(v, lane);
+  const int k = lane >> 1, b1 = u1 + k / T2, b2 = u2 + k % T2;
+  if (k < T1 * T2 && b1 < a.nb1 && b2 < a.nb2)
+    a.part[2 * ((size_t)sl * three_elems(nb, a.m) + ((size_t)mu * a.nn + ni) * nb * nb + (size_t)(a.lo1 + b1) * nb +
+                a.lo2 + b2) + (lane & 1)] = v[0];
 }
 
 // same-neighbour sums sum_i x_i D_mu(i, b) for every bin: one workgroup per
@@ -247,6 +283,46 @@ __global__ void finalize3_kernel(const double* acc, int nb, int m, int subtract,
   out[2 * i + 1] = sg * vi;
 }
 
+template <typename T, int T1, int T2>
+void launch_tile3(const ThreeArgs& a, hipStream_t s) {
+  const int groups = (tiles3(a.nb1, T1) * tiles3(a.nb2, T2) + 3) / 4;
+  hipLaunchKernelGGL((contract3_kernel<T, T1, T2>), dim3(a.nn * groups, 5, THREE_SLICES), dim3(256), 0, s, a);
+}
+template <typename T, int T1>
+void launch_row3(const ThreeArgs& a, int t2, hipStream_t s) {
+  switch (t2) {
+    case 2: return launch_tile3<T, T1, 2>(a, s);
+    case 3: return launch_tile3<T, T1, 3>(a, s);
+    case 4: return launch_tile3<T, T1, 4>(a, s);
+    case 5: return launch_tile3<T, T1, 5>(a, s);
+    default: return launch_tile3<T, T1, 6>(a, s);
+  }
+}
+// The tile shape of the least work: binary64 operations of a tile (four per
+// product, two conversions per record, four more for the centre factor at
+// slot 1, the sign at slot 2, about twelve per centre) times the tiles,
+// surplus bins of the last ones included.
+template <typename T>
+void launch_contract3(const ThreeArgs& a, hipStream_t s) {
+  int best1 = 0, best2 = 0;
+  int64_t least = INT64_MAX;
+  for (int t1 = 2; t1 <= 5; ++t1)
+    for (int t2 = 2; t2 <= 6; ++t2) {
+      const int64_t work = (int64_t)tiles3(a.nb1, t1) * tiles3(a.nb2, t2) * (4 * t1 * t2 + 6 * t1 + 3 * t2 + 12);
+      if (work < least) {
+        least = work;
+        best1 = t1;
+        best2 = t2;
+      }
+    }
+  switch (best1) {
+    case 2: return launch_row3<T, 2>(a, best2, s);
+    case 3: return launch_row3<T, 3>(a, best2, s);
+    case 4: return launch_row3<T, 4>(a, best2, s);
+    default: return launch_row3<T, 5>(a, best2, s);
+  }
+}
+
 }  // namespace
 
 template <typename T>
@@ -255,13 +331,12 @@ hipError_t launch_three(const ThreeArgs& a, hipStream_t s) {
   if (a.nb < 1 || a.nb > FPCF4_NBINS_SUPPORTED || a.m < 0 || a.m > 2 * a.n4) return hipErrorInvalidValue;
   if (a.lo1 < 0 || a.nb1 < 1 || a.lo1 + a.nb1 > a.nb || a.lo2 < 0 || a.nb2 < 1 || a.lo2 + a.nb2 > a.nb)
     return hipErrorInvalidValue;
-  const BinTiles bt1 = bin_tiles(a.nb1), bt2 = bin_tiles(a.nb2);
-  hipLaunchKernelGGL(contract3_kernel<T>, dim3(a.nn * bt1.nt * bt2.nt, 5, THREE_SLICES), dim3(256), 0, s, a);
+  launch_contract3<T>(a, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the same-neighbour sums exist where both slots share bins and records
   if (a.lo1 == a.lo2 && a.nb1 == a.nb2 && a.rec2 == a.rec && a.par1 == nullptr && a.par2 == nullptr)
-    hipLaunchKernelGGL(diag3_kernel<T>, dim3(5, THREE_SLICES, bt1.nt), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(diag3_kernel<T>, dim3(5, THREE_SLICES, bin_tiles(a.nb1).nt), dim3(256), 0, s, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t elems2 = 2 * three_elems(a.nb, a.m);
