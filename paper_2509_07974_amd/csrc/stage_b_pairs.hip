@@ -667,9 +667,15 @@ void contract_pair_kernel(PairArgs a) {
 // binary64: the same work items on v_mfma_f64_16x16x4_f64, no operand split,
 // no scaling, binary64 accumulation over the whole slice.  K-step = 2 centres
 // x (re, im): lane L holds k = L / 16, i.e. centre 2 ks + k / 2, part k % 2.
-// The left operand y = x A is staged as complex values and each lane builds
+// The left operand y = x A is staged as complex values and each lane reads
 // its [y_r, -y_i] / [y_i, y_r] entry; the right operand entry is the real or
-// imaginary part of B(b2) C(b3) for the lane's column.
+// imaginary part of B(b2) C(b3) for the lane's column.  Which component and
+// sign a lane takes is fixed: addresses and sign flips, no selections.
+// Bound by the matrix instructions (84 clocks each back to back, which
+// binary64 vector instructions do not overlap): 60000 centres, 12 bins, nmax 10
+// take 18.8 ms at that rate and 25.9 in all, 29.0 with both parts of the right
+// operand formed and one selected.  Chunks of 16 centres (half the LDS, a
+// third more waves) took 27.9.
 // ---------------------------------------------------------------------------
 struct cd {
   double r, i;
@@ -772,16 +778,29 @@ __global__ __launch_bounds__(64 * pair_waves(NBLK, NBC)) void contract_pair_f64_
     b2c[t] = colok[t] ? j / n3 : 0;
     b3c[t] = colok[t] ? j % n3 : 0;
   }
+  // this lane's k: centre 2 ks + kq / 2, part kq % 2 (imaginary: pk).  Its
+  // components and signs are fixed, so that an operand costs a sign flip and
+  // no selection.
+  const int kq = lane >> 4;
+  const bool pk = kq & 1;
+  const int cfirst = pk ? 1 : 0;
+  const unsigned bsign = pk ? 0u : 0x80000000u;
+  auto flip = [](double v, unsigned sign) -> double {
+    const unsigned long long u = __double_as_longlong(v);
+    return __longlong_as_double((long long)(u ^ ((unsigned long long)sign << 32)));
+  };
   // this lane's left-operand row in each row tile: (block, re/im, b1)
   int rblk[MT], rb1[MT];
-  bool rpart[MT], rok[MT];
+  int ypart[MT];        // component of y it takes, and its sign
+  unsigned ysign[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int r = 16 * m + (lane & 15);
-    rok[m] = r < mrows;
-    const int rr = rok[m] ? r : 0;
+    const int rr = r < mrows ? r : 0;   // a row past the last repeats row 0 and is not stored
     rblk[m] = rr / (2 * n1);
-    rpart[m] = (rr % (2 * n1)) >= n1;
+    const bool imag = (rr % (2 * n1)) >= n1;
+    ypart[m] = imag != pk;
+    ysign[m] = !imag && pk ? 0x80000000u : 0u;
     rb1[m] = rr % n1;
   }
   d4 acc[MT][NT];
@@ -790,8 +809,6 @@ __global__ __launch_bounds__(64 * pair_waves(NBLK, NBC)) void contract_pair_f64_
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[m][t] = d4{0.0, 0.0, 0.0, 0.0};
 
-  const int kq = lane >> 4;
-  const bool pk = kq & 1;
   const int nchunks = (ncent + PKC - 1) / PKC;
   if (ncent > 0) {
     issue(0);
@@ -808,15 +825,15 @@ __global__ __launch_bounds__(64 * pair_waves(NBLK, NBC)) void contract_pair_f64_
       double bv[NT];
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const cd b = Bs[buf][b2c[t]][cc], c = Cs[buf][b3c[t]][cc];
-        bv[t] = pk ? b.r * c.i + b.i * c.r : b.r * c.r - b.i * c.i;
+        // real part b_r c_r + (-b_i) c_i, imaginary part b_r c_i + b_i c_r
+        const cd b = Bs[buf][b2c[t]][cc];
+        const double* c = &Cs[buf][b3c[t]][cc].r;
+        bv[t] = __builtin_fma(b.r, c[cfirst], flip(b.i, bsign) * c[1 - cfirst]);
       }
 #pragma unroll
       for (int m = 0; m < MT; ++m) {
-        const cd y = Ys[buf][rblk[m]][rb1[m]][cc];
         // [y_r, -y_i] on real-output rows, [y_i, y_r] on imaginary-output rows
-        double av = rpart[m] ? (pk ? y.r : y.i) : (pk ? -y.i : y.r);
-        av = rok[m] ? av : 0.0;
+        const double av = flip((&Ys[buf][rblk[m]][rb1[m]][cc].r)[ypart[m]], ysign[m]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[m][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv[t], acc[m][t], 0, 0, 0);
       }
