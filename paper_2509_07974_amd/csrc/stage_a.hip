@@ -114,9 +114,14 @@ __host__ __device__ constexpr int max_units(const PassPlan& P) {
 // whose passes fit 132 accumulators, at least four from nmax 5 on (4PCF
 // plan) or at least two (3PCF plan, measured best at record order 5: two
 // passes of 54 units ahead of one and four); binary64 (two registers per
-// accumulator): passes of at most 72.
+// accumulator): passes of at most 105, which two waves per SIMD hold (the
+// few registers spilled at 90 and more are not the accumulators').  Every pass
+// reads each neighbour and forms its first power, so that fewer are faster:
+// 40000 galaxies, 12 bins, stage (a) with passes of at most 72 / 105: nmax 3
+// 11.5 / 9.1 ms, 5 13.2 / 12.1, 8 21.3 / 15.5, 10 23.0 / 17.0, 12 26.4 / 20.3.
+// Passes above 105 spill accumulators (nmax 6 13.8 / 22.3, 16 28.6 / 95).
 __host__ __device__ constexpr int choose_waves(int n, bool fp64) {
-  const int lim = fp64 ? 72 : 132;
+  const int lim = fp64 ? 105 : 132;
   int w = 1;
   while (w < 8 && max_units(plan_exact(n, w)) > lim) w *= 2;
   if (!fp64 && !is3(n) && n >= 5 && w < 4) w = 4;
