@@ -18,7 +18,7 @@ size_t cells_sort_temp_bytes(int64_t n);
 hipError_t cells_build(const double*, const double*, const double*, const double*, const double*,
                        int64_t, const Grid&, uint32_t*, uint32_t*, int32_t*, int32_t*, void*, size_t,
                        void*, int, int32_t*, int32_t*, hipStream_t);
-hipError_t cells_centre_order(const uint32_t*, int64_t, const Grid&, uint32_t*, uint32_t*, int32_t*,
+hipError_t cells_centre_order(const uint32_t*, const int32_t*, int64_t, const Grid&, uint32_t*, uint32_t*, int32_t*,
                               int32_t*, void*, size_t, hipStream_t);
 hipError_t cells_map_centres(const int64_t*, int64_t, const int32_t*, int32_t*, hipStream_t);
 size_t natural_tmp_bytes(int64_t ntrip, int nmax, int nphi);
@@ -92,6 +92,7 @@ struct PlanInfo {
   // create-time temporaries inside the region
   size_t t_raw, t_key_a, t_key_b, t_idx_a, t_idx_b, t_inv, t_sort, t_cent64;
   size_t base = 0;             // workspace without the octets
+  size_t o_order = 0, order_bytes = 0;                // a subset's processing order
   size_t o_upload, upload_bytes, o_zero, zero_bytes;   // host tables, buffers cleared at creation
   size_t o_octets[TREE_LEVELS_MAX + 1] = {};   // octets of the matrix-core pair kernel
   size_t total = 0;
@@ -251,6 +252,9 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   // a workspace without room for them still serves with the vector kernel
   if (P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax))
     for (int d = 0; d <= P.tree_levels; ++d) P.o_octets[d] = take(octet_bytes(n));
+  // likewise the order in which a tile of listed centres is worked off
+  P.order_bytes = opts->centers && P.ntiles == 1 && P.ncent <= P.n ? (size_t)P.ncent * 4 : 0;
+  P.o_order = take(P.order_bytes);
   // likewise the partials of the contraction's extra slices
   P.o_ppart_fill = P.o_ppart;
   if (P.pslices_fill > P.pslices) P.o_ppart_fill = take((size_t)P.pslices_fill * P.prows * P.nb * P.nb * 8);
@@ -302,6 +306,7 @@ struct fpcf4_request {
   std::vector<char> stepped;
   const PairPlanHost* pplan = nullptr;   // the contraction plan uploaded into the workspace (4PCF)
   std::vector<char> upload;              // the tables as uploaded, until the copy has completed
+  const int32_t* order = nullptr;   // of a tile of listed centres, or null: as listed
   bool full = false;            // the workspace has the `total` bytes, not only the `base`
   bool want_counts = false;
   bool no_events = false;       // allocation-free path: never create profiling events
@@ -495,10 +500,19 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
       int64_t* c64 = reinterpret_cast<int64_t*>(reg + P.t_cent64);
       HIPCHK(hipMemcpyAsync(c64, hc.data(), hc.size() * 8, hipMemcpyHostToDevice, s));
       HIPCHK(cells_map_centres(c64, P.ncent, inv, centres, s));
+      // neighbouring centres side by side, so that they share what they read
+      // (8192 of 10^7 galaxies, 16 bins to 200', nmax 15: stage (a) 29.5 ms as
+      // listed, 27.4 in Morton order)
+      if (R->full && P.order_bytes > 0) {
+        int32_t* order = R->at<int32_t>(P.o_order);
+        HIPCHK(cells_centre_order(key_b, centres, P.ncent, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a,
+                                  order, sort_tmp, P.sort_tmp, s));
+        R->order = order;
+      }
     }
   } else {
     // key_a / idx_a are free again after the sort; reuse them for the Morton sort
-    HIPCHK(cells_centre_order(key_b, n, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a, centres,
+    HIPCHK(cells_centre_order(key_b, nullptr, n, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a, centres,
                               sort_tmp, P.sort_tmp, s));
   }
   if (octets && matrix_scale(bb, n, R->ms[0])) {
@@ -558,6 +572,7 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
   a.cat.cell_start = R->at<int32_t>(P.o_cells);
   a.cat.g = R->grid;
   a.centres = R->at<int32_t>(P.o_centres) + c0;
+  a.order = R->order;
   a.cgal = a.cat.gal;
   a.ncent = ncent;
   a.nb = P.nb;

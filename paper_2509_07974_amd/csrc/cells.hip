@@ -137,11 +137,12 @@ __device__ __forceinline__ uint32_t spread16(uint32_t v) {
   return v;
 }
 
-__global__ void morton_kernel(const uint32_t* skey, int64_t n, int ncx, uint32_t* mkey,
+// pos: the sorted positions to order, or null for all
+__global__ void morton_kernel(const uint32_t* skey, const int32_t* pos, int64_t n, int ncx, uint32_t* mkey,
                               int32_t* idx) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const uint32_t k = skey[i];
+    const uint32_t k = skey[pos ? pos[i] : i];
     const uint32_t cy = k / (uint32_t)ncx, cx = k - cy * (uint32_t)ncx;
     mkey[i] = spread16(cx) | (spread16(cy) << 1);
     idx[i] = (int32_t)i;
@@ -202,12 +203,13 @@ hipError_t cells_build(const double* x, const double* y, const double* g1, const
   return hipGetLastError();
 }
 
-// Morton-ordered list of all sorted positions (uses key_b from cells_build;
-// mkey_a and idx_a are overwritten).
-hipError_t cells_centre_order(const uint32_t* skey, int64_t n, const Grid& g, uint32_t* mkey_a,
+// Morton-ordered list of all n sorted positions, or with pos the indices of n
+// listed ones in that order (uses key_b from cells_build; mkey_a, mkey_b and
+// idx_a are overwritten).
+hipError_t cells_centre_order(const uint32_t* skey, const int32_t* pos, int64_t n, const Grid& g, uint32_t* mkey_a,
                               uint32_t* mkey_b, int32_t* idx_a, int32_t* out, void* sort_tmp,
                               size_t sort_tmp_bytes, hipStream_t s) {
-  hipLaunchKernelGGL(morton_kernel, dim3(grid1d(n)), dim3(256), 0, s, skey, n, g.ncx, mkey_a, idx_a);
+  hipLaunchKernelGGL(morton_kernel, dim3(grid1d(n)), dim3(256), 0, s, skey, pos, n, g.ncx, mkey_a, idx_a);
   // cell coordinates below 2^b interleave into keys below 2^(2b); spread16
   // keeps 16 bits of each coordinate
   const int b = bits_for((uint64_t)std::max(g.ncx, g.ncy));

@@ -161,6 +161,7 @@ constexpr int SCHED_WORDS = 8 * SCHED_STRIDE;     // counters of one launch
 struct StageAArgs {
   SortedCat cat;
   const int32_t* centres;   // positions in cgal of this tile's centres
+  const int32_t* order;     // the order to work them off in (indices into centres), or null: as they come
   const void* cgal;         // Gal<T> records of the centres: cat.gal, or base pseudo-galaxies
   int32_t ncent;
   int32_t nb;

@@ -556,7 +556,7 @@ __device__ __forceinline__ void pass_body(const StageAArgs& a,
           const int hi = (int)(((int64_t)a.ncent * (xcd + 1)) >> 3);
           const int c = atomicAdd(a.work_counter + SCHED_STRIDE * xcd, 1);
           if (lo + c < hi) {
-            idx = lo + c;
+            idx = a.order ? a.order[lo + c] : lo + c;
             break;
           }
           ++xs;

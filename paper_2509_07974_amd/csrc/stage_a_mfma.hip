@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void s
       }
     }
     if (idx < 0) break;
-    idx = __builtin_amdgcn_readfirstlane(idx);
+    idx = __builtin_amdgcn_readfirstlane(a.order ? a.order[idx] : idx);
     grp = __builtin_amdgcn_readfirstlane(grp);
     const Gal<float> gi = cgal[a.centres[idx]];
     const double xi = gi.x, yi = gi.y;

@@ -112,3 +112,17 @@ def test_workspace_without_operands(fp):
     with pytest.raises(fp.Fpcf4Error):
         fp.Request(*cat.arrays(), edges, 5, precision="fp16",
                    workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("precision,nmax", [("fp16", 6), ("fp16", 2), ("fp64", 3)])
+@pytest.mark.parametrize("n", [1, 65, 700])
+def test_listed_centres(fp, precision, nmax, n):
+    """Listed centres are worked off in another order; blocks come as listed,
+    those of the whole catalogue bit for bit."""
+    cat = synth.uniform_catalogue(17, 700, 40.0)
+    edges = synth.log_edges(1.0, 18.0, 3)
+    cen = np.random.default_rng(n).permutation(700)[:n]
+    whole = fp.debug_multipoles(*cat.arrays(), edges, nmax, precision=precision)
+    got = fp.debug_multipoles(*cat.arrays(), edges, nmax, precision=precision, centers=cen)
+    for a, b in zip(got, whole):
+        assert np.array_equal(a, b[cen])
