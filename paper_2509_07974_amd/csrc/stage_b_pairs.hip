@@ -230,10 +230,11 @@ constexpr int PKC = 32;             // centres per staged chunk (two K-steps of 
 // partial region of every item) and none of them empty.  Slices of PAIR_SUB
 // centres for large tiles; with `fill`, as many more as a small tile needs for
 // PAIR_FILL workgroups in a launch, of at least PAIR_SLICE_MIN centres: 2000
-// centres at nmax 3 have 74 work items, and one slice of them left most of the
-// chip idle (binary64 480 us, fp16 203; with 15 slices 70 and 27, and 5 more to
-// add them).  Where the items fill it nothing is gained: 30011 centres at nmax
-// 8 3.16 ms with 4 slices as with 6.
+// centres at nmax 3 have 95 work items (42 and 53 in two launches), and one
+// slice of them left most of the chip idle (binary64 480 us, fp16 203; with 13
+// slices 70 and 27, and 5 more to add them).  Where the items nearly fill it
+// nothing is gained or lost: 30011 centres at nmax 7 3.16 ms with 4 slices as
+// with 9.
 constexpr int PAIR_FILL = 2048;       // 8 workgroups per CU, two rounds of those resident
 constexpr int PAIR_SLICE_MIN = 128;
 int pair_slices(int64_t ncent, const PairPlanHost& pp, int nb, bool fill, int64_t cap) {
