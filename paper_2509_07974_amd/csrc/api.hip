@@ -76,7 +76,7 @@ struct PlanInfo {
   size_t sort_tmp = 0;
   // persistent buffers
   size_t o_gal, o_cells, o_centres, o_e2, o_edges, o_counters, o_bbox, o_bad,
-      o_pairs, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
+      o_pairs, o_faint, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
       o_aos, o_region, o_pitems, o_pout, o_ppart, o_ppart_fill, o_csums, o_cmap;
   // contraction work items (each distinct product of three blocks once)
   int pslices = 0, pslices_fill = 0;   // of the contraction: in a workspace of `base` bytes, of `total` bytes
@@ -218,6 +218,7 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.o_bbox = take(kCatStats * 8 + 16);
   P.o_bad = P.o_bbox + kCatStats * 8;   // read back with the statistics
   P.o_pairs = take(16);
+  P.o_faint = take((TREE_LEVELS_MAX + 1) * 4);   // build_octets, of the galaxies and each reduced catalogue
   P.o_corr = take(P.corr_bytes);
   P.o_acc3 = take(P.acc3_bytes);
   P.o_ups = take(P.ups_bytes);
@@ -323,13 +324,15 @@ namespace {
 
 // The scales of the matrix-core pair kernel for a catalogue, or false where
 // the vector kernel has to serve.  Every operand is two binary16 values, 22
-// significant bits with an absolute floor of 2^-25.  The scales put w g and w
-// below 2^7 and their squares below 2^15, and the triple-block weights below
-// 2^15, so the floors are 2^-32, 2^-40 and 2^-40 of the largest value of
-// each.  binary32 has no such floor, so the matrix cores take catalogues whose
-// largest weight is at most 2^5 times its rms: every floor is then at most
-// 2^-24 of the rms of its own weight, as for binary32 rounding.  The kernel's
-// 32-bit byte offsets reach kMatrixMax neighbours.
+// significant bits with an absolute floor of 2^-25.  The scales put the largest
+// value of w g, of w and of their squares and cubes between 2^14 and 2^15, so
+// that the floor is about 2^-40 of it.  binary32 has no such floor, and the
+// weights near a centre may be far below the largest of the catalogue: 1e-3 of
+// it leaves 1e-9 of the cube, of which the floor is 1e-3.  Which octets hold
+// too little is therefore looked at where they are made (build_octets), and one
+// such octet sends the whole catalogue to the vector kernel; a weight above
+// 2^5 times the rms does so at once.  The kernel's 32-bit byte offsets reach
+// kMatrixMax neighbours.
 constexpr int64_t kMatrixMax = int64_t(1) << 25;
 static_assert(kMatrixMax / 8 * OCTET_BYTES <= (int64_t(1) << 32), "32-bit octet offsets");
 int exponent_above(double v) {   // v < 2^e
@@ -339,18 +342,16 @@ int exponent_above(double v) {   // v < 2^e
 }
 bool matrix_scale(const double* st, int64_t n, MatScale& m) {
   if (n >= kMatrixMax) return false;
-  const double big[2] = {st[4], st[5]}, sq[2] = {st[6], st[7]};
+  const double big[2] = {std::sqrt(st[4]), st[5]}, sq[2] = {st[6], st[7]};
   for (int k = 0; k < 2; ++k) {
     if (big[k] == 0.0) continue;
     if (!(big[k] > 1e-9 && big[k] < 1e9)) return false;
     if (!(big[k] * big[k] * (double)n <= 1024.0 * sq[k])) return false;
   }
-  const int eg = exponent_above(big[0]), ew = exponent_above(big[1]);
-  // two components below 2^eg: (w g)^2 and |w g|^2 below 2^(2 eg + 1), the
-  // triple-block weights below 2^(3 eg + 1.5)
-  const int lg = 7 - eg, lw = 7 - ew;
-  const int ex[NWEIGHTS] = {lg, lg, 2 * lg, 2 * lg, lw, 2 * lg, 2 * lw,
-                            13 - 3 * eg, 13 - 3 * eg, 13 - 3 * eg, 13 - 3 * eg, 14 - 3 * ew};
+  const double g = big[0], w = big[1];
+  const int g1 = 15 - exponent_above(g), g2 = 15 - exponent_above(g * g), g3 = 15 - exponent_above(g * g * g);
+  const int w1 = 15 - exponent_above(w), w2 = 15 - exponent_above(w * w), w3 = 15 - exponent_above(w * w * w);
+  const int ex[NWEIGHTS] = {g1, g1, g2, g2, w1, g2, w2, g3, g3, g3, g3, w3};
   for (int f = 0; f < NWEIGHTS; ++f) m.inv[f] = std::ldexp(1.0, -ex[f]);
   return true;
 }
@@ -516,7 +517,7 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
                               sort_tmp, P.sort_tmp, s));
   }
   if (octets && matrix_scale(bb, n, R->ms[0])) {
-    HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->ws + P.o_octets[0], s));
+    HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->ws + P.o_octets[0], R->at<unsigned>(P.o_faint), s));
     R->mm[0] = true;
   }
   // reduced catalogues of the tree approximation, on the same search grid
@@ -527,11 +528,15 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
                          P.tree_delta1 * std::ldexp(1.0, d - 1), g, reg + P.t_red,
                          R->ws + P.o_rgal[d - 1], R->at<int32_t>(P.o_rcell[d - 1]), &m, s, nullptr, st));
     if (octets && m > 0 && matrix_scale_reduced(st, m, R->ms[d])) {
-      HIPCHK(build_octets(R->at<GalR<float>>(P.o_rgal[d - 1]), m, R->ms[d], R->ws + P.o_octets[d], s));
+      HIPCHK(build_octets(R->at<GalR<float>>(P.o_rgal[d - 1]), m, R->ms[d], R->ws + P.o_octets[d],
+                          R->at<unsigned>(P.o_faint) + d, s));
       R->mm[d] = true;
     }
   }
+  unsigned faint[TREE_LEVELS_MAX + 1] = {};
+  if (octets) HIPCHK(hipMemcpyAsync(faint, R->ws + P.o_faint, sizeof faint, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  for (int d = 0; d <= TREE_LEVELS_MAX; ++d) R->mm[d] = R->mm[d] && !faint[d];
   return FPCF4_OK;
 }
 

@@ -17,8 +17,8 @@
 
 namespace fpcf4 {
 
-// Per block: min / max of x and y, max |w g| component, max |w|, sum |w g|^2,
-// sum w^2 (kCatStats values), and the count of non-finite galaxies, which
+// Per block: min / max of x and y, max |w g|^2, max |w|, sum |w g|^2, sum w^2
+// (kCatStats values), and the count of non-finite galaxies, which
 // enter nothing else.
 __device__ __forceinline__ void stat_join(double* a, const double* b) {
   a[0] = fmin(a[0], b[0]);
@@ -60,8 +60,8 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const double* x, con
       ++nbad;
       continue;
     }
-    const double ga = fabs(wv * a), gb = fabs(wv * b);
-    const double o[kCatStats] = {xv, xv, yv, yv, fmax(ga, gb), fabs(wv), ga * ga + gb * gb, wv * wv};
+    const double ga = wv * a, gb = wv * b, gg = ga * ga + gb * gb;
+    const double o[kCatStats] = {xv, xv, yv, yv, gg, fabs(wv), gg, wv * wv};
     stat_join(v, o);
   }
   stat_block(v);

@@ -116,8 +116,8 @@ __host__ __device__ inline BinTiles bin_tiles(int nb) {
   return BinTiles{nt > 0 ? (nb + nt - 1) / nt : 0, nt};
 }
 
-// Catalogue statistics: min x, max x, min y, max y, max |w g| component,
-// max |w|, sum |w g|^2, sum w^2.
+// Catalogue statistics: min x, max x, min y, max y, max |w g|^2, max |w|,
+// sum |w g|^2, sum w^2.
 constexpr int kCatStats = 8;
 
 // Sorted catalogue on the device.
@@ -131,7 +131,7 @@ struct SortedCat {
 // Operands of the matrix-core pair kernel (stage_a_mfma.hip).  Per weight of a
 // neighbour (Re, Im w g, Re, Im (w g)^2, w, |w g|^2, w^2, then the triple-block
 // weights Re, Im (w g)^3, Re, Im |w g|^2 w g, w^3) a power-of-two scale that
-// keeps its values below 2^15; f and inv are each other's inverses.
+// keeps its values below 2^15 (about: rounding may reach it).
 constexpr int NWEIGHTS = 12;
 // Record orders that it serves.  Its cost steps with the number of its row
 // orders (one up to orders k = 25, two above), the vector kernel's grows with
@@ -149,8 +149,13 @@ struct MatScale {
 // triple-block weights in the layout the kernel loads.
 constexpr int OCTET_BYTES = 768;   // a multiple of 256: the low byte of an offset carries a mask
 size_t octet_bytes(int64_t n);     // of n neighbours
+// *faint becomes non-zero if some octet's weights are too small for their
+// scale (a power or product of them below OCTET_MIN throughout the octet):
+// the operands would hold them in fewer than 22 bits, so that only the vector
+// kernel may take this catalogue.  The caller clears it.
+constexpr double OCTET_MIN = 0.125;   // 2^-3: the low part's floor of 2^-25 is 2^-22 of it
 template <typename Rec>
-hipError_t build_octets(const Rec* gal, int64_t n, const MatScale& ms, void* out, hipStream_t s);
+hipError_t build_octets(const Rec* gal, int64_t n, const MatScale& ms, void* out, unsigned* faint, hipStream_t s);
 
 // Stage (a) hands out centres from one queue per XCD.  Device-scope atomics on
 // one line are served one after the other by the memory side (about 12 ns each

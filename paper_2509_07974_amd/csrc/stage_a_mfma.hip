@@ -803,8 +803,12 @@ __device__ __forceinline__ double weight_of(const GalR<float>& q, int f) {
 }
 
 constexpr int kOctetParts = 30;   // 4 pairs of positions, 26 rows
+// weights whose second component is the next one: real and imaginary part
+__device__ __forceinline__ bool complex_weight(int f) { return f == FA || f == FC || f == NF || f == NF + 2; }
+__device__ __forceinline__ bool second_part(int f) { return f > 0 && complex_weight(f - 1); }
 template <typename Rec>
-__global__ __launch_bounds__(256) void octet_kernel(const Rec* gal, int64_t n, MatScale ms, unsigned char* out) {
+__global__ __launch_bounds__(256) void octet_kernel(const Rec* gal, int64_t n, MatScale ms, unsigned char* out,
+                                                    unsigned* faint) {
   const int64_t parts = ((n + 7) / 8) * kOctetParts;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < parts; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t oc = i / kOctetParts;
@@ -832,6 +836,17 @@ __global__ __launch_bounds__(256) void octet_kernel(const Rec* gal, int64_t n, M
       v[j] = low ? (_Float16)(x - (float)h) : h;
     }
     *reinterpret_cast<half8v*>(o + 128 + 16 * row) = v;
+    if (!low && !none && !second_part(f)) {
+      // the largest of a real or complex weight; a last octet of fewer than
+      // eight counts with the one before it, since a galaxy or two alone may
+      // well have a small shear
+      double most = 0.0;
+      for (int64_t q = 8 * oc + 8 > n && oc > 0 ? 8 * oc - 8 : 8 * oc; q < 8 * oc + 8 && q < n; ++q) {
+        most = fmax(most, fabs(weight_of(gal[q], f) / ms.inv[f]));
+        if (complex_weight(f)) most = fmax(most, fabs(weight_of(gal[q], f + 1) / ms.inv[f + 1]));
+      }
+      if (most > 0.0 && most < OCTET_MIN) *faint = 1u;   // every writer stores the same
+    }
   }
 }
 #endif
@@ -842,15 +857,16 @@ __global__ __launch_bounds__(256) void octet_kernel(const Rec* gal, int64_t n, M
 size_t octet_bytes(int64_t n) { return (size_t)((n + 7) / 8) * OCTET_BYTES; }
 
 template <typename Rec>
-hipError_t build_octets(const Rec* gal, int64_t n, const MatScale& ms, void* out, hipStream_t s) {
+hipError_t build_octets(const Rec* gal, int64_t n, const MatScale& ms, void* out, unsigned* faint, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t blocks = (((n + 7) / 8) * sa::kOctetParts + 255) / 256;
   hipLaunchKernelGGL(sa::octet_kernel<Rec>, dim3((unsigned)(blocks < 16384 ? blocks : 16384)), dim3(256), 0, s, gal,
-                     n, ms, static_cast<unsigned char*>(out));
+                     n, ms, static_cast<unsigned char*>(out), faint);
   return hipGetLastError();
 }
-template hipError_t build_octets<Gal<float>>(const Gal<float>*, int64_t, const MatScale&, void*, hipStream_t);
-template hipError_t build_octets<GalR<float>>(const GalR<float>*, int64_t, const MatScale&, void*, hipStream_t);
+template hipError_t build_octets<Gal<float>>(const Gal<float>*, int64_t, const MatScale&, void*, unsigned*, hipStream_t);
+template hipError_t build_octets<GalR<float>>(const GalR<float>*, int64_t, const MatScale&, void*, unsigned*,
+                                              hipStream_t);
 #endif
 
 }  // namespace fpcf4
