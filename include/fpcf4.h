@@ -340,9 +340,12 @@ fpcf4_status fpcf4_plan(const fpcf4_catalogue *cat, const fpcf4_bins *bins,
                         const fpcf4_options *opts, size_t *device_bytes,
                         int64_t *ntiles);
 
-/* The smallest workspace a request runs in: fpcf4_plan() bytes without the
- * operand copies of the faster pair kernel (96 bytes per galaxy in the mixed
- * paths).  fpcf4_request_create() takes any size from this one on. */
+/* The smallest workspace a request runs in.  fpcf4_plan() adds to it what only
+ * makes an estimate faster: the operand copies of the matrix-core pair kernel
+ * where it may serve (96 bytes per galaxy, mixed paths from nmax 5), the working
+ * order of listed centres (4 bytes each), and the partial sums of more slices
+ * of the contraction.  fpcf4_request_create() takes any size from the smallest
+ * on and uses as much of this as fits, in this order. */
 fpcf4_status fpcf4_plan_min(const fpcf4_catalogue *cat, const fpcf4_bins *bins,
                             const fpcf4_options *opts, size_t *device_bytes);
 

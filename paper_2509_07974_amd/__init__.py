@@ -344,8 +344,8 @@ def profile_read() -> dict:
 def plan(n: int, edges, nmax: int, precision="fp64", ncenters=None, tile_centers: int = 0,
          smallest: bool = False):
     """(device_bytes, ntiles) of a request with these sizes; with `smallest`
-    the bytes it runs in at least (without the operand copies of the faster
-    pair kernel)."""
+    the bytes it runs in at least (without the operand copies of the
+    matrix-core pair kernel, the centre order and the contraction's extra slices)."""
     z = np.zeros(1)
     m = _Marshal(z, z, z, z, z, edges, nmax, precision, True, None, tile_centers, None)
     m.cat.n = int(n)

@@ -63,6 +63,9 @@ constexpr size_t kPairPartialBudget = size_t(48) << 30;
 // maxima.
 constexpr int kSchedCounters = 2 * SCHED_WORDS;
 constexpr int kCounterWords = kSchedCounters + MAXIMA_WORDS;
+// Neighbours that the matrix-core pair kernel's 32-bit byte offsets reach.
+constexpr int64_t kMatrixMax = int64_t(1) << 25;
+static_assert(kMatrixMax / 8 * OCTET_BYTES <= (int64_t(1) << 32), "32-bit octet offsets");
 
 struct PlanInfo {
   int64_t n = 0, ncent = 0, tile = 0, ntiles = 0, ldc = 0;
@@ -77,9 +80,10 @@ struct PlanInfo {
   // persistent buffers
   size_t o_gal, o_cells, o_centres, o_e2, o_edges, o_counters, o_bbox, o_bad,
       o_pairs, o_faint, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
-      o_aos, o_region, o_pitems, o_pout, o_ppart, o_ppart_fill, o_csums, o_cmap;
+      o_aos, o_region, o_pitems, o_pout, o_csums, o_cmap;
   // contraction work items (each distinct product of three blocks once)
-  int pslices = 0, pslices_fill = 0;   // of the contraction: in a workspace of `base` bytes, of `total` bytes
+  int pslices = 0, pslices_fill = 0;   // of the contraction: at least, and as many as fill the chip
+  size_t slice_bytes = 0;              // partials of one
   int64_t pitems = 0, prows = 0;
   // distinct degenerate-term sums
   int csums = 0, cpair = 0, cmap = 0;
@@ -91,11 +95,14 @@ struct PlanInfo {
   size_t region = 0;           // records of one tile, or create-time temporaries
   // create-time temporaries inside the region
   size_t t_raw, t_key_a, t_key_b, t_idx_a, t_idx_b, t_inv, t_sort, t_cent64;
-  size_t base = 0;             // workspace without the octets
-  size_t o_order = 0, order_bytes = 0;                // a subset's processing order
+  // Behind the `core` lie, where the workspace has room for them, the octets of
+  // the matrix-core pair kernel (galaxies, then each reduced catalogue) and a
+  // subset's processing order, and last the partials of the contraction's
+  // slices, `pslices` of them at least.
+  size_t core = 0, octets[TREE_LEVELS_MAX + 1] = {}, order_bytes = 0;
+  size_t base = 0;             // smallest workspace: core and pslices slices
   size_t o_upload, upload_bytes, o_zero, zero_bytes;   // host tables, buffers cleared at creation
-  size_t o_octets[TREE_LEVELS_MAX + 1] = {};   // octets of the matrix-core pair kernel
-  size_t total = 0;
+  size_t total = 0;            // all of it, with pslices_fill slices
 };
 
 fpcf4_status validate_common(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
@@ -192,8 +199,8 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
         return fail(FPCF4_E_DEVICE, "internal: contraction plan leaves an output unassigned");
     P.pitems = (int64_t)pp.items.size();
     P.prows = pp.total_rows * P.nb;
-    const size_t slice_bytes = (size_t)P.prows * P.nb * P.nb * 8;
-    const int64_t fit = std::clamp<int64_t>((int64_t)(kPairPartialBudget / std::max<size_t>(slice_bytes, 1)), 1,
+    P.slice_bytes = (size_t)P.prows * P.nb * P.nb * 8;
+    const int64_t fit = std::clamp<int64_t>((int64_t)(kPairPartialBudget / std::max<size_t>(P.slice_bytes, 1)), 1,
                                             PAIR_SLICES_MAX);
     P.pslices = pair_slices(P.tile, pp, P.nb, false, fit);
     P.pslices_fill = pair_slices(P.tile, pp, P.nb, true, fit);
@@ -223,7 +230,6 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.o_acc3 = take(P.acc3_bytes);
   P.o_ups = take(P.ups_bytes);
   P.zero_bytes = off - P.o_zero;
-  P.o_ppart = take((size_t)P.pslices * P.prows * P.nb * P.nb * 8);
   P.o_cpart = take(P.corr_bytes * CORR_SLICES);
   P.o_part3 = take(P.acc3_bytes * THREE_SLICES);
   for (int d = 1; d <= P.tree_levels; ++d) {
@@ -248,18 +254,16 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   if (P.tree_levels > 0) P.t_red = ttake(reduced_scratch_bytes(n));
   P.region = std::max(t, up((size_t)P.ldc * rec_per_centre));
   P.o_region = take(P.region);
-  P.base = off;
-  // octets of the matrix-core pair kernel (mixed paths), last, so that
-  // a workspace without room for them still serves with the vector kernel
+  P.core = off;
+  P.base = off + up(P.pslices * P.slice_bytes);
+  // a reduced catalogue has at most n cells, how many is not known before it is built
   if (P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax))
-    for (int d = 0; d <= P.tree_levels; ++d) P.o_octets[d] = take(octet_bytes(n));
-  // likewise the order in which a tile of listed centres is worked off
+    for (int d = 0; d <= P.tree_levels; ++d)
+      if (d > 0 || P.n < kMatrixMax) P.octets[d] = up(octet_bytes(std::min<int64_t>(n, kMatrixMax - 1)));
   P.order_bytes = opts->centers && P.ntiles == 1 && P.ncent <= P.n ? (size_t)P.ncent * 4 : 0;
-  P.o_order = take(P.order_bytes);
-  // likewise the partials of the contraction's extra slices
-  P.o_ppart_fill = P.o_ppart;
-  if (P.pslices_fill > P.pslices) P.o_ppart_fill = take((size_t)P.pslices_fill * P.prows * P.nb * P.nb * 8);
-  P.total = off;
+  for (size_t b : P.octets) off += b;
+  off += up(P.order_bytes);
+  P.total = off + up(std::max(P.pslices, P.pslices_fill) * P.slice_bytes);
   return FPCF4_OK;
 }
 
@@ -308,7 +312,9 @@ struct fpcf4_request {
   const PairPlanHost* pplan = nullptr;   // the contraction plan uploaded into the workspace (4PCF)
   std::vector<char> upload;              // the tables as uploaded, until the copy has completed
   const int32_t* order = nullptr;   // of a tile of listed centres, or null: as listed
-  bool full = false;            // the workspace has the `total` bytes, not only the `base`
+  char* octets[TREE_LEVELS_MAX + 1] = {};   // room for them, or null
+  double* ppart = nullptr;          // partials of `slices` slices of the contraction
+  int slices = 1;
   bool want_counts = false;
   bool no_events = false;       // allocation-free path: never create profiling events
   std::vector<hipEvent_t> ev;   // 4 per profiled step
@@ -333,8 +339,6 @@ namespace {
 // such octet sends the whole catalogue to the vector kernel; a weight above
 // 2^5 times the rms does so at once.  The kernel's 32-bit byte offsets reach
 // kMatrixMax neighbours.
-constexpr int64_t kMatrixMax = int64_t(1) << 25;
-static_assert(kMatrixMax / 8 * OCTET_BYTES <= (int64_t(1) << 32), "32-bit octet offsets");
 int exponent_above(double v) {   // v < 2^e
   int e = 0;
   if (v > 0.0) std::frexp(v, &e);
@@ -382,10 +386,23 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   if (!wsp) return fail(FPCF4_E_INVALID_ARG, "null workspace");
   if (reinterpret_cast<uintptr_t>(wsp) % ALIGN) return fail(FPCF4_E_INVALID_ARG, "workspace not 256-byte aligned");
   if (bytes < P.base) return fail(FPCF4_E_BUDGET, "workspace %zu bytes < planned %zu", bytes, P.base);
-  R->full = bytes >= P.total;
-  const bool octets = P.precision != FPCF4_FP64 && matrix_order(P.order, P.nmax) && R->full;
   R->edges.assign(bins->edges, bins->edges + P.nb + 1);
   R->ws = static_cast<char*>(wsp);
+  size_t at = P.core;
+  auto room = [&](size_t b) -> char* {   // b bytes more, if the least slices still fit behind them
+    if (b == 0 || at + up(b) + P.pslices * P.slice_bytes > bytes) return nullptr;
+    char* p = R->ws + at;
+    at += up(b);
+    return p;
+  };
+  bool octets = false;
+  for (int d = 0; d <= P.tree_levels; ++d) octets |= (R->octets[d] = room(P.octets[d])) != nullptr;
+  int32_t* order_buf = reinterpret_cast<int32_t*>(room(P.order_bytes));
+  R->ppart = reinterpret_cast<double*>(R->ws + at);
+  R->slices = P.pslices;
+  if (P.slice_bytes > 0)
+    R->slices = (int)std::clamp<int64_t>((int64_t)((bytes - at) / P.slice_bytes), P.pslices,
+                                         std::max(P.pslices, P.pslices_fill));
   R->stream = static_cast<hipStream_t>(opts->stream);
   R->stepped.assign((size_t)P.ntiles, 0);
   hipStream_t s = R->stream;
@@ -504,11 +521,10 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
       // neighbouring centres side by side, so that they share what they read
       // (8192 of 10^7 galaxies, 16 bins to 200', nmax 15: stage (a) 29.5 ms as
       // listed, 27.4 in Morton order)
-      if (R->full && P.order_bytes > 0) {
-        int32_t* order = R->at<int32_t>(P.o_order);
+      if (order_buf) {
         HIPCHK(cells_centre_order(key_b, centres, P.ncent, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a,
-                                  order, sort_tmp, P.sort_tmp, s));
-        R->order = order;
+                                  order_buf, sort_tmp, P.sort_tmp, s));
+        R->order = order_buf;
       }
     }
   } else {
@@ -516,8 +532,8 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     HIPCHK(cells_centre_order(key_b, nullptr, n, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a, centres,
                               sort_tmp, P.sort_tmp, s));
   }
-  if (octets && matrix_scale(bb, n, R->ms[0])) {
-    HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->ws + P.o_octets[0], R->at<unsigned>(P.o_faint), s));
+  if (R->octets[0] && matrix_scale(bb, n, R->ms[0])) {
+    HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->octets[0], R->at<unsigned>(P.o_faint), s));
     R->mm[0] = true;
   }
   // reduced catalogues of the tree approximation, on the same search grid
@@ -527,8 +543,8 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     HIPCHK(reduced_build(x, y, g1, g2, w, n, bb[0], bb[2], bb[1], bb[3],
                          P.tree_delta1 * std::ldexp(1.0, d - 1), g, reg + P.t_red,
                          R->ws + P.o_rgal[d - 1], R->at<int32_t>(P.o_rcell[d - 1]), &m, s, nullptr, st));
-    if (octets && m > 0 && matrix_scale_reduced(st, m, R->ms[d])) {
-      HIPCHK(build_octets(R->at<GalR<float>>(P.o_rgal[d - 1]), m, R->ms[d], R->ws + P.o_octets[d],
+    if (R->octets[d] && m > 0 && matrix_scale_reduced(st, m, R->ms[d])) {
+      HIPCHK(build_octets(R->at<GalR<float>>(P.o_rgal[d - 1]), m, R->ms[d], R->octets[d],
                           R->at<unsigned>(P.o_faint) + d, s));
       R->mm[d] = true;
     }
@@ -543,7 +559,7 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
 // neighbours of the pair kernels: the matrix-core kernel's operands
 void matrix_args(const fpcf4_request* R, StageAArgs& a) {
   for (int d = 0; d <= R->P.tree_levels; ++d) {
-    a.octets[d] = R->mm[d] ? R->ws + R->P.o_octets[d] : nullptr;
+    a.octets[d] = R->mm[d] ? R->octets[d] : nullptr;
     a.ms[d] = R->ms[d];
   }
   a.host_edges = R->edges.data();
@@ -635,8 +651,8 @@ fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {
     pl.nb = P.nb;
     pl.nmax = P.nmax;
     pl.precision = P.precision;
-    pl.nslices = pair_slices(ncent, *R->pplan, P.nb, R->full, R->full ? P.pslices_fill : P.pslices);
-    pl.part = R->at<double>(R->full ? P.o_ppart_fill : P.o_ppart);
+    pl.nslices = pair_slices(ncent, *R->pplan, P.nb, R->slices > P.pslices, R->slices);
+    pl.part = R->ppart;
     pl.total_rows = P.prows;
     pl.ups = R->at<double>(P.o_ups);
     HIPCHK(launch_contract_pairs(pl, s));

@@ -1,0 +1,62 @@
+"""Workspace sizes: what a plan reserves, and what serves in less."""
+import numpy as np
+import pytest
+
+from helpers import ensure_built
+
+EDGES = np.geomspace(1.0, 50.0, 5)
+
+
+@pytest.fixture(scope="module")
+def fp():
+    ensure_built()
+    import paper_2509_07974_amd as m
+    return m
+
+
+def extra(fp, n, nmax, precision, **kw):
+    return fp.plan(n, EDGES, nmax, precision, **kw)[0] - fp.plan(n, EDGES, nmax, precision, smallest=True, **kw)[0]
+
+
+def test_operands_reserved_where_they_serve(fp):
+    """96 bytes per galaxy for the matrix-core pair kernel, which takes
+    catalogues of fewer than 2^25 galaxies."""
+    kw = {"tile_centers": 64}     # one slice of the contraction
+    below, above = 2 ** 25 - 8, 2 ** 25
+    assert abs(extra(fp, below, 8, "fp16", **kw) - 96 * below) < 4096
+    assert extra(fp, above, 8, "fp16", **kw) < 4096
+    assert extra(fp, below, 8, "fp64", **kw) < 4096
+
+
+def test_extra_slices_reserved_once(fp):
+    """One slice of the contraction at least; two fill the chip at 256 centres,
+    three at 384, and the first is not reserved again for them."""
+    one, two = (extra(fp, n, 3, "fp64") for n in (256, 384))
+    assert one > 0 and abs(two - 2 * one) <= 1024
+
+
+@pytest.mark.gpu
+def test_parts_of_a_workspace(fp):
+    """Bytes between the smallest and the planned size serve what fits them: a
+    workspace without room for the centre order still holds the operands of
+    the pair kernel (the same records, bit for bit), the smallest one does not."""
+    import torch
+    import synth
+    cat = synth.uniform_catalogue(31, 700, 40.0)
+    edges = synth.log_edges(1.0, 18.0, 3)
+    cen = np.random.default_rng(1).permutation(700)[:200]
+
+    def run(take_off):
+        need, _ = fp.plan(cat.n, edges, 6, "fp16", ncenters=200)
+        least, _ = fp.plan(cat.n, edges, 6, "fp16", ncenters=200, smallest=True)
+        ws = torch.empty(least if take_off is None else need - take_off, dtype=torch.uint8, device="cuda")
+        r = fp.Request(*cat.arrays(), edges, 6, precision="fp16", centers=cen, workspace=ws)
+        while r.step():
+            pass
+        out = r.finalize()
+        r.close()
+        return out
+
+    whole = run(0)
+    assert np.array_equal(run(512), whole)
+    assert not np.array_equal(run(None), whole)
