@@ -376,7 +376,12 @@ class Request:
         self.bytes = int(nbytes.value)
         self.ntiles = int(ntiles.value)
         if workspace is None:
-            workspace = torch.empty(self.bytes, dtype=torch.uint8, device="cuda")
+            try:
+                workspace = torch.empty(self.bytes, dtype=torch.uint8, device="cuda")
+            except torch.OutOfMemoryError:   # the least it runs in
+                least = C.c_size_t(0)
+                check(lib().fpcf4_plan_min(*self.m.refs(), C.byref(least)))
+                workspace = torch.empty(int(least.value), dtype=torch.uint8, device="cuda")
         self.bytes = min(self.bytes, workspace.numel())   # too small a one is refused below
         self.workspace = workspace
         s = self.m.stream

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "fpcf4_internal.hpp"
+#include "workspace.hpp"
 
 namespace fpcf4 {
 hipError_t cells_stats(const double*, const double*, const double*, const double*, const double*,
@@ -277,6 +278,14 @@ void setup_pool() {
     uint64_t thr = UINT64_MAX;
     (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
   });
+}
+
+hipError_t get_workspace(const PlanInfo& P, hipStream_t s, void** ws, size_t* bytes) {
+  return reserve(P.total, P.base, hipErrorOutOfMemory, [&](size_t b) {
+    const hipError_t e = hipMallocAsync(ws, b, s);
+    if (e != hipSuccess) (void)hipGetLastError();   // or the next launch's check reports it
+    return e;
+  }, bytes);
 }
 
 std::mutex g_prof_mu;
@@ -733,6 +742,7 @@ struct StreamBuffers {
     *out = nullptr;
     hipError_t e = hipMallocAsync(out, std::max<size_t>(bytes, 256), s);
     if (e == hipSuccess) p.push_back(*out);
+    else (void)hipGetLastError();   // or the next launch's check reports it
     return e;
   }
   ~StreamBuffers() {
@@ -1037,9 +1047,10 @@ fpcf4_status estimate_4pcf_multipoles(const fpcf4_catalogue* cat, const fpcf4_bi
   setup_pool();
   hipStream_t s = static_cast<hipStream_t>(opts->stream);
   void* ws = nullptr;
-  HIPCHK(hipMallocAsync(&ws, P.total, s));
+  size_t bytes = 0;
+  HIPCHK(get_workspace(P, s, &ws, &bytes));
   fpcf4_request* R = nullptr;
-  st = fpcf4_request_create(cat, bins, opts, ws, P.total, &R);
+  st = fpcf4_request_create(cat, bins, opts, ws, bytes, &R);
   for (int64_t t = 0; st == FPCF4_OK && t < P.ntiles; ++t) st = fpcf4_request_step(R, t);
   if (st == FPCF4_OK) st = fpcf4_request_finalize(R, upsilon, out_mem);
   fpcf4_request_destroy(R);
@@ -1098,10 +1109,11 @@ fpcf4_status estimate_4pcf_multipoles_tree(const fpcf4_catalogue* cat, const fpc
   setup_pool();
   hipStream_t s = static_cast<hipStream_t>(opts->stream);
   void* ws = nullptr;
-  HIPCHK(hipMallocAsync(&ws, P.total, s));
+  size_t bytes = 0;
+  HIPCHK(get_workspace(P, s, &ws, &bytes));
   fpcf4_request* R = new (std::nothrow) fpcf4_request();
   if (!R) st = fail(FPCF4_E_OUT_OF_MEMORY, "host allocation failed");
-  if (st == FPCF4_OK) st = request_init(cat, bins, opts, ws, P.total, R, 4, 0, tree);
+  if (st == FPCF4_OK) st = request_init(cat, bins, opts, ws, bytes, R, 4, 0, tree);
   for (int64_t t = 0; st == FPCF4_OK && t < P.ntiles; ++t) st = request_step(R, t, true);
   if (st == FPCF4_OK) st = fpcf4_request_finalize(R, upsilon, out_mem);
   delete R;
@@ -1127,10 +1139,11 @@ fpcf4_status estimate_3pcf_multipoles(const fpcf4_catalogue* cat, const fpcf4_bi
   setup_pool();
   hipStream_t s = static_cast<hipStream_t>(o.stream);
   void* ws = nullptr;
-  HIPCHK(hipMallocAsync(&ws, P.total, s));
+  size_t bytes = 0;
+  HIPCHK(get_workspace(P, s, &ws, &bytes));
   fpcf4_request* R = new (std::nothrow) fpcf4_request();
   if (!R) st = fail(FPCF4_E_OUT_OF_MEMORY, "host allocation failed");
-  if (st == FPCF4_OK) st = request_init(cat, bins, &o, ws, P.total, R, 3, m);
+  if (st == FPCF4_OK) st = request_init(cat, bins, &o, ws, bytes, R, 3, m);
   for (int64_t t = 0; st == FPCF4_OK && t < P.ntiles; ++t) st = request_step(R, t, true);
   if (st == FPCF4_OK) st = fpcf4_request_finalize(R, upsilon3, out_mem);
   delete R;
@@ -1167,18 +1180,31 @@ fpcf4_status estimate_3pcf_multipoles_doubletree(const fpcf4_catalogue* cat, con
   setup_pool();
   hipStream_t s = static_cast<hipStream_t>(o.stream);
   void* ws = nullptr;
-  HIPCHK(hipMallocAsync(&ws, P.total, s));
-  fpcf4_request* R = new (std::nothrow) fpcf4_request();
-  if (!R) st = fail(FPCF4_E_OUT_OF_MEMORY, "host allocation failed");
-  if (st == FPCF4_OK) st = request_init(cat, bins, &o, ws, P.total, R, 3, m, tree);
-  if (base) {
-    if (st == FPCF4_OK && P.n > 0) st = run_3pcf_basetree(R, cat, bins, base);
-  } else {
-    // neighbours on the tree's grids, base points the galaxies: the tiled path
-    for (int64_t t = 0; st == FPCF4_OK && t < P.ntiles; ++t) st = request_step(R, t, true);
+  size_t bytes = 0;
+  HIPCHK(get_workspace(P, s, &ws, &bytes));
+  auto run = [&]() -> fpcf4_status {
+    fpcf4_request* R = new (std::nothrow) fpcf4_request();
+    if (!R) return fail(FPCF4_E_OUT_OF_MEMORY, "host allocation failed");
+    fpcf4_status r = request_init(cat, bins, &o, ws, bytes, R, 3, m, tree);
+    if (base) {
+      if (r == FPCF4_OK && P.n > 0) r = run_3pcf_basetree(R, cat, bins, base);
+    } else {
+      // neighbours on the tree's grids, base points the galaxies: the tiled path
+      for (int64_t t = 0; r == FPCF4_OK && t < P.ntiles; ++t) r = request_step(R, t, true);
+    }
+    if (r == FPCF4_OK) r = fpcf4_request_finalize(R, upsilon3, out_mem);
+    delete R;
+    return r;
+  };
+  st = run();
+  if (base && st == FPCF4_E_OUT_OF_MEMORY && bytes > P.base) {
+    // the base grids' own buffers did not fit beside a workspace of the planned size
+    HIPCHK(hipFreeAsync(ws, s));
+    HIPCHK(hipStreamSynchronize(s));
+    bytes = P.base;
+    HIPCHK(hipMallocAsync(&ws, bytes, s));
+    st = run();
   }
-  if (st == FPCF4_OK) st = fpcf4_request_finalize(R, upsilon3, out_mem);
-  delete R;
   hipError_t e = hipFreeAsync(ws, s);
   if (st == FPCF4_OK && e != hipSuccess) return fail(FPCF4_E_DEVICE, "hipFreeAsync: %s", hipGetErrorString(e));
   return st;
@@ -1309,10 +1335,11 @@ fpcf4_status fpcf4_debug_multipoles(const fpcf4_catalogue* cat, const fpcf4_bins
   setup_pool();
   hipStream_t s = static_cast<hipStream_t>(opts->stream);
   void* ws = nullptr;
-  HIPCHK(hipMallocAsync(&ws, P.total, s));
+  size_t bytes = 0;
+  HIPCHK(get_workspace(P, s, &ws, &bytes));
   fpcf4_request* R = new fpcf4_request();
   R->want_counts = true;
-  st = request_init(cat, bins, opts, ws, P.total, R);
+  st = request_init(cat, bins, opts, ws, bytes, R);
   const Layout& L = R->P.L;
   const int nb = P.nb, n = P.nmax;
   std::vector<int32_t> hcnt;

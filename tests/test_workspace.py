@@ -1,8 +1,13 @@
-"""Workspace sizes: what a plan reserves, and what serves in less."""
+"""Workspace sizes: what a plan reserves, and what an estimate falls back to
+when the device has no room for it (host logic, no GPU)."""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 
-from helpers import ensure_built
+from helpers import ROOT, ensure_built
 
 EDGES = np.geomspace(1.0, 50.0, 5)
 
@@ -33,6 +38,36 @@ def test_extra_slices_reserved_once(fp):
     three at 384, and the first is not reserved again for them."""
     one, two = (extra(fp, n, 3, "fp64") for n in (256, 384))
     assert one > 0 and abs(two - 2 * one) <= 1024
+
+
+PROGRAM = """
+#include <cstdio>
+#include "workspace.hpp"
+int main() {
+  // bytes that the device has, status 2 = no memory, 5 = another failure
+  struct Case { std::size_t have; int other; } cases[] = {{100, 0}, {60, 0}, {10, 0}, {100, 5}};
+  for (auto c : cases) {
+    std::size_t bytes = 0;
+    int asked = 0;
+    int st = fpcf4::reserve(std::size_t(80), std::size_t(50), 2, [&](std::size_t b) {
+      ++asked;
+      return c.other ? c.other : b <= c.have ? 0 : 2;
+    }, &bytes);
+    std::printf("%d %zu %d\\n", st, bytes, asked);
+  }
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_smallest_size_where_the_planned_one_does_not_fit(tmp_path):
+    src = tmp_path / "t.cpp"
+    src.write_text(PROGRAM)
+    exe = tmp_path / "t"
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2509_07974_amd", "csrc"), str(src), "-o",
+                    str(exe)], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split("\n")[:-1]
+    assert out == ["0 80 1", "0 50 2", "2 50 2", "5 80 1"]
 
 
 @pytest.mark.gpu
