@@ -26,9 +26,14 @@
 // Mapping on CDNA4 (wave64):
 //  * one wave owns one (centre, group of bins) at a time (per-XCD queues over
 //    the Morton-ordered centre list, with stealing); no barriers between
-//    waves.  Within a block of 64 centres the widest bins come first and all
-//    centres of the block take the same bin together, so that the waves of an
-//    XCD read the same galaxies at the same time;
+//    waves.  The widest bins come first and all centres of a queue take the
+//    same group of bins together, so that the waves of an XCD read the same
+//    galaxies at the same time: the octets are 96 bytes a galaxy, and in a dense
+//    field one row of cells of one group is as large as a share of L2.  With
+//    the groups in turn within blocks of 64 centres, six groups were in flight
+//    at once (1e6 galaxies, 12 bins to 100', nmax 8, 65536 or 16384 centres at 3,
+//    10, 60 and 120 galaxies per square arcmin: 52, 189, 134 and 197 ms, against
+//    48, 172, 111 and 162 now);
 //  * the annulus is a list of octets (8 consecutive sorted galaxies, aligned)
 //    with an 8-bit mask of those inside the row segment.  A chunk is 8
 //    octets: lane l forms neighbour l&7 of octet l>>3.  r^2 is formed in
@@ -361,11 +366,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void s
       const int hi = (int)(((int64_t)a.ncent * (xcd + 1)) >> 3);
       const unsigned u = (unsigned)__builtin_amdgcn_readfirstlane(next);
       if (u < (unsigned)(hi - lo) * (unsigned)ng) {
-        const unsigned blk = u / (64u * (unsigned)ng), rem = u - blk * 64u * (unsigned)ng;
-        const int b0 = lo + (int)(blk * 64u);
-        const unsigned nc = (unsigned)imin(64, hi - b0);
-        grp = (int)(rem / nc);
-        idx = b0 + (int)(rem - (unsigned)grp * nc);
+        const unsigned nc = (unsigned)(hi - lo);
+        grp = (int)(u / nc);
+        idx = lo + (int)(u - (unsigned)grp * nc);
         next = request();
         break;
       }
