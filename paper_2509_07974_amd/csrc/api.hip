@@ -541,7 +541,11 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     HIPCHK(cells_centre_order(key_b, nullptr, n, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a, centres,
                               sort_tmp, P.sort_tmp, s));
   }
-  if (R->octets[0] && matrix_scale(bb, n, R->ms[0])) {
+  // no area (all on a line): no density to judge by
+  auto sparse = [&](int64_t m) {
+    return (double)m * rmax * rmax <= matrix_density_max(P.order, P.nmax) * (wx * wy) || !(wx * wy > 0.0);
+  };
+  if (R->octets[0] && sparse(n) && matrix_scale(bb, n, R->ms[0])) {
     HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->octets[0], R->at<unsigned>(P.o_faint), s));
     R->mm[0] = true;
   }
@@ -552,7 +556,7 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     HIPCHK(reduced_build(x, y, g1, g2, w, n, bb[0], bb[2], bb[1], bb[3],
                          P.tree_delta1 * std::ldexp(1.0, d - 1), g, reg + P.t_red,
                          R->ws + P.o_rgal[d - 1], R->at<int32_t>(P.o_rcell[d - 1]), &m, s, nullptr, st));
-    if (R->octets[d] && m > 0 && matrix_scale_reduced(st, m, R->ms[d])) {
+    if (R->octets[d] && m > 0 && sparse(m) && matrix_scale_reduced(st, m, R->ms[d])) {
       HIPCHK(build_octets(R->at<GalR<float>>(P.o_rgal[d - 1]), m, R->ms[d], R->octets[d],
                           R->at<unsigned>(P.o_faint) + d, s));
       R->mm[d] = true;

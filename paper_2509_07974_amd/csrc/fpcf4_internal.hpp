@@ -136,11 +136,26 @@ constexpr int NWEIGHTS = 12;
 // Record orders that it serves.  Its cost steps with the number of its row
 // orders (one up to orders k = 25, two above), the vector kernel's grows with
 // every order: 1e5 galaxies at 2.5 per square arcmin, 12 bins 1-80', vector /
-// matrix kernel: 4PCF nmax 3 26.3 / 28.3 ms, 4 29.1 / 31.3, 5 37.2 / 31.5, 8
-// 43.7 / 31.6, 10 49.5 / 32.3; 3PCF records of order 7 26.7 / 27.6, 8 28.5 /
-// 27.9, 11 32.8 / 27.9, 12 34.3 / 36.1, 13 45.7 / 36.5, 16 52.4 / 38.3.
+// matrix kernel: 4PCF nmax 3 26.3 / 30.5 ms, 4 29.1 / 30.5, 5 37.3 / 30.8, 8
+// 43.3 / 29.9, 10 48.9 / 30.4, 15 76.0 / 41.7; 3PCF records of order 7 26.7 /
+// 27.7, 8 28.4 / 27.6, 11 32.7 / 27.7, 12 34.3 / 36.2, 13 45.8 / 36.5, 16
+// 52.6 / 38.0.
 __host__ __device__ constexpr bool matrix_order(int order, int n) {
   return order == 3 ? n >= 8 && n != 12 : n >= 5;
+}
+// Largest number of neighbours per square of the outermost radius up to which
+// it serves those orders.  In a dense field it waits for its operands, 96 bytes a
+// neighbour where the vector kernel reads 32, and is no faster at one order than
+// at the next, so that the vector kernel is ahead at the lower ones.  Stage
+// (a) of 16384 centres of 1e6 galaxies, 12 bins to 100', vector / matrix kernel:
+// 4PCF nmax 5 at 10, 20, 30 and 80 galaxies per square arcmin 177 / 171 (65536
+// centres), 258 / 257 (likewise), 106 / 107, 142 / 152, nmax 6 at 80 and 120 153 / 152, 156 / 164, nmax 7
+// at 120 165 / 161; 3PCF records of order 8 at 1, 3 and 30 5.0 / 4.9, 11.5 /
+// 12.0, 101 / 106, of order 9 at 30 and 60 106 / 106, 124 / 128, of order 10 at
+// 60 and 120 132 / 129, 135 / 138, of order 11 at 120 139 / 139.
+__host__ __device__ constexpr double matrix_density_max(int order, int n) {
+  if (order == 3) return n == 8 ? 2e4 : n == 9 ? 2e5 : n == 10 ? 8e5 : 1e300;
+  return n == 5 ? 1.5e5 : n == 6 ? 8e5 : 1e300;
 }
 struct MatScale {
   double inv[NWEIGHTS];   // reciprocals of the scales
