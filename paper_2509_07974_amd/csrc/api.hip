@@ -14,7 +14,7 @@
 
 namespace fpcf4 {
 hipError_t cells_stats(const double*, const double*, const double*, const double*, const double*,
-                       int64_t, double*, unsigned*, double*, hipStream_t);
+                       int64_t, double, double*, unsigned*, unsigned*, double*, hipStream_t);
 size_t cells_sort_temp_bytes(int64_t n);
 hipError_t cells_build(const double*, const double*, const double*, const double*, const double*,
                        int64_t, const Grid&, uint32_t*, uint32_t*, int32_t*, int32_t*, void*, size_t,
@@ -80,7 +80,7 @@ struct PlanInfo {
   size_t sort_tmp = 0;
   // persistent buffers
   size_t o_gal, o_cells, o_centres, o_e2, o_edges, o_counters, o_bbox, o_bad,
-      o_pairs, o_faint, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
+      o_pairs, o_faint, o_coarse, o_ups, o_corr, o_cpart, o_acc3, o_part3, o_xg, o_xw, o_counts,
       o_aos, o_region, o_pitems, o_pout, o_csums, o_cmap;
   // contraction work items (each distinct product of three blocks once)
   int pslices = 0, pslices_fill = 0;   // of the contraction: at least, and as many as fill the chip
@@ -227,6 +227,7 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.o_bad = P.o_bbox + kCatStats * 8;   // read back with the statistics
   P.o_pairs = take(16);
   P.o_faint = take((TREE_LEVELS_MAX + 1) * 4);   // build_octets, of the galaxies and each reduced catalogue
+  P.o_coarse = take(kCoarseWords * 4);
   P.o_corr = take(P.corr_bytes);
   P.o_acc3 = take(P.acc3_bytes);
   P.o_ups = take(P.ups_bytes);
@@ -478,8 +479,10 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     x = cat->x; y = cat->y; g1 = cat->g1; g2 = cat->g2; w = cat->w;
   }
   unsigned* bad = R->at<unsigned>(P.o_bad);
-  HIPCHK(cells_stats(x, y, g1, g2, w, n, reinterpret_cast<double*>(reg + P.t_key_a), bad,
-                     R->at<double>(P.o_bbox), s));
+  const double rmax = bins->edges[P.nb];
+  const double coarse = rmax / 8.0;   // the largest cell of the search grid
+  HIPCHK(cells_stats(x, y, g1, g2, w, n, coarse, reinterpret_cast<double*>(reg + P.t_key_a), bad,
+                     R->at<unsigned>(P.o_coarse), R->at<double>(P.o_bbox), s));
   double bb[kCatStats + 1];
   HIPCHK(hipMemcpyAsync(bb, R->ws + P.o_bbox, sizeof bb, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
@@ -495,10 +498,13 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   // outer edge / 24).  A row segment of the matrix-core kernel costs about
   // seven candidates of rounding to octets: with 3.2 e / h segments and
   // 6.7 e h candidates per unit density outside an annulus of outer edge e the
-  // cost is least at 1.8 galaxies per cell, which sparse catalogues get.
-  const double rmax = bins->edges[P.nb];
+  // cost is least at 1.8 galaxies per cell, which sparse catalogues get.  The
+  // area is that of the coarse cells that hold galaxies: with the bounding box,
+  // two patches of 1e5 galaxies (10 per square arcmin) 3000' apart got cells of
+  // 9' for 4' and took 166 ms of stage (a) for 142 (nmax 3).
   const double wx = bb[1] - bb[0], wy = bb[3] - bb[2];
-  double h = std::max(rmax / 48.0, std::min(1.35 * std::sqrt(wx * wy / (double)n), rmax / 8.0));
+  const double area = std::min(wx * wy, bb[8] * coarse * coarse);
+  double h = std::max(rmax / 48.0, std::min(1.35 * std::sqrt(area / (double)n), coarse));
   for (;;) {
     const double ncx = std::floor(wx / h) + 1.0, ncy = std::floor(wy / h) + 1.0;
     if (ncx * ncy <= (double)P.ncell_cap) break;
@@ -541,9 +547,13 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     HIPCHK(cells_centre_order(key_b, nullptr, n, g, key_a, reinterpret_cast<uint32_t*>(inv), idx_a, centres,
                               sort_tmp, P.sort_tmp, s));
   }
-  // no area (all on a line): no density to judge by
+  // No area (all on a line): no density to judge by.  Cells that their number has
+  // forced above the coarse size hold few neighbours of a bin, and the matrix
+  // kernel pays more for the rest (1e5 galaxies at 10 per square arcmin and one
+  // 20000' away, nmax 8: 254 ms, the vector kernel 206).
   auto sparse = [&](int64_t m) {
-    return (double)m * rmax * rmax <= matrix_density_max(P.order, P.nmax) * (wx * wy) || !(wx * wy > 0.0);
+    return h <= coarse &&
+           ((double)m * rmax * rmax <= matrix_density_max(P.order, P.nmax) * area || !(area > 0.0));
   };
   if (R->octets[0] && sparse(n) && matrix_scale(bb, n, R->ms[0])) {
     HIPCHK(build_octets(R->at<Gal<float>>(P.o_gal), n, R->ms[0], R->octets[0], R->at<unsigned>(P.o_faint), s));

@@ -18,8 +18,9 @@
 namespace fpcf4 {
 
 // Per block: min / max of x and y, max |w g|^2, max |w|, sum |w g|^2, sum w^2
-// (kCatStats values), and the count of non-finite galaxies, which
-// enter nothing else.
+// (kPartStats values), the occupied coarse cells, and the count of non-finite
+// galaxies, which enter nothing else.
+constexpr int kPartStats = 8;
 __device__ __forceinline__ void stat_join(double* a, const double* b) {
   a[0] = fmin(a[0], b[0]);
   a[1] = fmax(a[1], b[1]);
@@ -32,26 +33,36 @@ __device__ __forceinline__ void stat_join(double* a, const double* b) {
 }
 // over the workgroup (256 threads), in a fixed order; thread 0 ends with all
 __device__ __forceinline__ void stat_block(double* v) {
-  __shared__ double s[4][kCatStats];
+  __shared__ double s[4][kPartStats];
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
-    double o[kCatStats];
+    double o[kPartStats];
 #pragma unroll
-    for (int k = 0; k < kCatStats; ++k) o[k] = __shfl_xor(v[k], d, 64);
+    for (int k = 0; k < kPartStats; ++k) o[k] = __shfl_xor(v[k], d, 64);
     stat_join(v, o);
   }
   const int wv = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0)
-    for (int k = 0; k < kCatStats; ++k) s[wv][k] = v[k];
+    for (int k = 0; k < kPartStats; ++k) s[wv][k] = v[k];
   __syncthreads();
   if (threadIdx.x == 0)
     for (int w = 1; w < 4; ++w) stat_join(v, s[w]);
 }
 
+// coarse cell of a coordinate, folded to 0 .. kCoarse - 1
+__device__ __forceinline__ int coarse_of(double v, double inv_c) {
+  const double q = floor(v * inv_c);
+  return (int)(q - kCoarse * floor(q * (1.0 / kCoarse))) & (kCoarse - 1);
+}
+
 __global__ __launch_bounds__(256) void stats_partial_kernel(const double* x, const double* y, const double* g1,
-                                                            const double* g2, const double* w, int64_t n,
-                                                            double* part /* [nblk][kCatStats] */, unsigned* bad) {
-  double v[kCatStats] = {INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
+                                                            const double* g2, const double* w, int64_t n, double inv_c,
+                                                            double* part /* [nblk][kPartStats] */, unsigned* bad,
+                                                            unsigned* coarse /* [kCoarseWords] */) {
+  __shared__ unsigned seen[kCoarseWords];
+  for (int q = (int)threadIdx.x; q < kCoarseWords; q += (int)blockDim.x) seen[q] = 0u;
+  __syncthreads();
+  double v[kPartStats] = {INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
   unsigned nbad = 0;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -61,26 +72,43 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const double* x, con
       continue;
     }
     const double ga = wv * a, gb = wv * b, gg = ga * ga + gb * gb;
-    const double o[kCatStats] = {xv, xv, yv, yv, gg, fabs(wv), gg, wv * wv};
+    const double o[kPartStats] = {xv, xv, yv, yv, gg, fabs(wv), gg, wv * wv};
     stat_join(v, o);
+    const int cell = coarse_of(yv, inv_c) * kCoarse + coarse_of(xv, inv_c);
+    atomicOr(&seen[cell >> 5], 1u << (cell & 31));
   }
   stat_block(v);
   if (threadIdx.x == 0)
-    for (int k = 0; k < kCatStats; ++k) part[blockIdx.x * kCatStats + k] = v[k];
+    for (int k = 0; k < kPartStats; ++k) part[blockIdx.x * kPartStats + k] = v[k];
   if (nbad) atomicAdd(bad, nbad);
+  __syncthreads();
+  // most bits are set by the first blocks: look before the atomic
+  for (int q = (int)threadIdx.x; q < kCoarseWords; q += (int)blockDim.x)
+    if (seen[q] & ~__hip_atomic_load(coarse + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(coarse + q, seen[q]);
 }
 
-__global__ __launch_bounds__(256) void stats_final_kernel(const double* part, int nblk, double* out) {
-  double v[kCatStats] = {INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
+__global__ __launch_bounds__(256) void stats_final_kernel(const double* part, int nblk, const unsigned* coarse,
+                                                          double* out) {
+  double v[kPartStats] = {INFINITY, -INFINITY, INFINITY, -INFINITY, 0.0, 0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < nblk; b += 256) {
-    double o[kCatStats];
+    double o[kPartStats];
 #pragma unroll
-    for (int k = 0; k < kCatStats; ++k) o[k] = part[b * kCatStats + k];
+    for (int k = 0; k < kPartStats; ++k) o[k] = part[b * kPartStats + k];
     stat_join(v, o);
   }
   stat_block(v);
   if (threadIdx.x == 0)
-    for (int k = 0; k < kCatStats; ++k) out[k] = v[k];
+    for (int k = 0; k < kPartStats; ++k) out[k] = v[k];
+  __shared__ int occ[256];
+  int c = 0;
+  for (int q = (int)threadIdx.x; q < kCoarseWords; q += 256) c += __popc(coarse[q]);
+  occ[threadIdx.x] = c;
+  __syncthreads();
+  for (int st = 128; st > 0; st >>= 1) {
+    if ((int)threadIdx.x < st) occ[threadIdx.x] += occ[threadIdx.x + st];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[kPartStats] = occ[0];
 }
 
 __device__ __forceinline__ int cell_of(double v, double v0, double inv_h, int nc) {
@@ -163,14 +191,15 @@ static inline int grid1d(int64_t n) {
   return (int)b;
 }
 
-// out[kCatStats] as stats_partial_kernel lists them; part holds
-// kCatStats doubles for each of up to max(1, n / 256) blocks.
+// out[kCatStats] as stats_partial_kernel lists them, with the number of coarse
+// cells of side c that hold galaxies (folded: at most kCoarse^2); part
+// holds kPartStats doubles for each of up to max(1, n / 256) blocks, coarse is zero.
 hipError_t cells_stats(const double* x, const double* y, const double* g1, const double* g2,
-                       const double* w, int64_t n, double* part, unsigned* bad, double* out,
-                       hipStream_t s) {
+                       const double* w, int64_t n, double c, double* part, unsigned* bad, unsigned* coarse,
+                       double* out, hipStream_t s) {
   const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>(2048, n / 256));
-  hipLaunchKernelGGL(stats_partial_kernel, dim3(nblk), dim3(256), 0, s, x, y, g1, g2, w, n, part, bad);
-  hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(256), 0, s, part, nblk, out);
+  hipLaunchKernelGGL(stats_partial_kernel, dim3(nblk), dim3(256), 0, s, x, y, g1, g2, w, n, 1.0 / c, part, bad, coarse);
+  hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(256), 0, s, part, nblk, coarse, out);
   return hipGetLastError();
 }
 

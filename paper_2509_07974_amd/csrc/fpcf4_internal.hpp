@@ -117,8 +117,11 @@ __host__ __device__ inline BinTiles bin_tiles(int nb) {
 }
 
 // Catalogue statistics: min x, max x, min y, max y, max |w g|^2, max |w|,
-// sum |w g|^2, sum w^2.
-constexpr int kCatStats = 8;
+// sum |w g|^2, sum w^2, occupied coarse cells.  The last are counted in a bitmap
+// of kCoarse x kCoarse cells that the plane is folded onto.
+constexpr int kCatStats = 9;
+constexpr int kCoarse = 256;
+constexpr int kCoarseWords = kCoarse * kCoarse / 32;
 
 // Sorted catalogue on the device.
 struct SortedCat {
