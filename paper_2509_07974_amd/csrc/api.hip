@@ -503,7 +503,12 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   // two patches of 1e5 galaxies (10 per square arcmin) 3000' apart got cells of
   // 9' for 4' and took 166 ms of stage (a) for 142 (nmax 3).
   const double wx = bb[1] - bb[0], wy = bb[3] - bb[2];
-  const double area = std::min(wx * wy, bb[8] * coarse * coarse);
+  // Where the box is larger than the bitmap, its cells share bits: m (-ln of the
+  // clear fraction) of m bits estimates how many they were; all set, the box.
+  constexpr double bits = (double)kCoarse * kCoarse;
+  const bool folded = std::max(wx, wy) > (kCoarse - 1) * coarse;
+  const double occupied = folded ? -bits * std::log1p(-bb[8] / bits) : bb[8];
+  const double area = std::min(wx * wy, occupied * coarse * coarse);
   double h = std::max(rmax / 48.0, std::min(1.35 * std::sqrt(area / (double)n), coarse));
   for (;;) {
     const double ncx = std::floor(wx / h) + 1.0, ncy = std::floor(wy / h) + 1.0;
