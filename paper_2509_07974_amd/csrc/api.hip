@@ -64,6 +64,8 @@ constexpr size_t kPairPartialBudget = size_t(48) << 30;
 // maxima.
 constexpr int kSchedCounters = 2 * SCHED_WORDS;
 constexpr int kCounterWords = kSchedCounters + MAXIMA_WORDS;
+constexpr int64_t kCellCapMin = int64_t(1) << 16;   // cells that the search grid may always have
+static_assert(kCellCapMin >= kCoarseWords, "the bitmap fits the cell starts");
 // Neighbours that the matrix-core pair kernel's 32-bit byte offsets reach.
 constexpr int64_t kMatrixMax = int64_t(1) << 25;
 static_assert(kMatrixMax / 8 * OCTET_BYTES <= (int64_t(1) << 32), "32-bit octet offsets");
@@ -179,14 +181,13 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.ldc = (tile + 15) / 16 * 16;
   P.ntiles = P.ncent > 0 ? (P.ncent + tile - 1) / tile : 0;
   const int64_t n = P.n > 0 ? P.n : 1;
-  P.ncell_cap = std::max<int64_t>(int64_t(1) << 16, 4 * n);
+  P.ncell_cap = std::max<int64_t>(kCellCapMin, 4 * n);
   P.sort_tmp = cells_sort_temp_bytes(n);
   const int nn = 2 * P.nmax + 1;
 
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += up(bytes); return o; };
   P.o_gal = take(n * (P.precision == FPCF4_FP64 ? sizeof(Gal<double>) : sizeof(Gal<float>)));
-  P.o_cells = take((P.ncell_cap + 1) * 4);
   P.o_centres = take((size_t)std::max<int64_t>(P.ncent, 1) * 4);
   P.o_counters = take(kCounterWords * 4);   // scheduling counters, then the scaling maxima
   P.ups_bytes = order == 4 ? (size_t)9 * P.nb * P.nb * P.nb * nn * nn * 16 : 0;
@@ -227,11 +228,12 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   P.o_bad = P.o_bbox + kCatStats * 8;   // read back with the statistics
   P.o_pairs = take(16);
   P.o_faint = take((TREE_LEVELS_MAX + 1) * 4);   // build_octets, of the galaxies and each reduced catalogue
-  P.o_coarse = take(kCoarseWords * 4);
   P.o_corr = take(P.corr_bytes);
   P.o_acc3 = take(P.acc3_bytes);
   P.o_ups = take(P.ups_bytes);
-  P.zero_bytes = off - P.o_zero;
+  // the coarse bitmap of the statistics takes the place of the first cell starts
+  P.o_cells = P.o_coarse = take((P.ncell_cap + 1) * 4);
+  P.zero_bytes = P.o_coarse + kCoarseWords * 4 - P.o_zero;
   P.o_cpart = take(P.corr_bytes * CORR_SLICES);
   P.o_part3 = take(P.acc3_bytes * THREE_SLICES);
   for (int d = 1; d <= P.tree_levels; ++d) {

@@ -40,6 +40,20 @@ def test_extra_slices_reserved_once(fp):
     assert one > 0 and abs(two - 2 * one) <= 1024
 
 
+# (n, nbins, nmax, precision, centres): bytes planned before there were smallest sizes
+SAVED = [((0, 1, 0, "fp64", None), 290048), ((1, 1, 0, "fp16", None), 287744), ((100, 4, 3, "fp64", 7), 1868288),
+         ((2000, 4, 3, "fp16", None), 9961984), ((2000, 12, 10, "fp16", 7), 165670400),
+         ((30000, 12, 8, "fp64", None), 1826300160), ((1000000, 12, 10, "fp64", None), 68465752064)]
+
+
+@pytest.mark.parametrize("case,saved", SAVED)
+def test_saved_sizes_still_serve(fp, case, saved):
+    """A program that keeps a workspace of a size planned earlier."""
+    n, nb, nmax, precision, cen = case
+    least, _ = fp.plan(n, np.geomspace(1, 50, nb + 1), nmax, precision, ncenters=cen, smallest=True)
+    assert least <= saved
+
+
 PROGRAM = """
 #include <cstdio>
 #include "workspace.hpp"
