@@ -187,6 +187,25 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
 
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += up(bytes); return o; };
+  // Records and their staging first, on a page of 4 KB each where they are large:
+  // the binary64 relayout between them takes 16.2 ms at 1e6 galaxies, 12 bins,
+  // nmax 10 then, and up to 19.7 where the buffers before them leave them elsewhere.
+  P.o_aos = take((size_t)P.tile * rec_per_centre);
+  // region: one tile of records, or the create-time temporaries
+  size_t t = 0;
+  auto ttake = [&](size_t bytes) { size_t o = t; t += up(bytes); return o; };
+  P.t_raw = ttake(n * 8 * 5);
+  P.t_key_a = ttake(n * 4);
+  P.t_key_b = ttake(n * 4);
+  P.t_idx_a = ttake(n * 4);
+  P.t_idx_b = ttake(n * 4);
+  P.t_inv = ttake(n * 4);
+  P.t_cent64 = ttake((size_t)std::max<int64_t>(P.ncent, 1) * 8);
+  P.t_sort = ttake(P.sort_tmp);
+  if (P.tree_levels > 0) P.t_red = ttake(reduced_scratch_bytes(n));
+  P.region = std::max(t, up((size_t)P.ldc * rec_per_centre));
+  if (off >= (size_t(1) << 20)) off = (off + 4095) & ~size_t(4095);
+  P.o_region = take(P.region);
   P.o_gal = take(n * (P.precision == FPCF4_FP64 ? sizeof(Gal<double>) : sizeof(Gal<float>)));
   P.o_centres = take((size_t)std::max<int64_t>(P.ncent, 1) * 4);
   P.o_counters = take(kCounterWords * 4);   // scheduling counters, then the scaling maxima
@@ -242,22 +261,7 @@ fpcf4_status make_plan(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   }
   P.o_xg = take((size_t)P.ldc * 2 * P.tsize);
   P.o_xw = take((size_t)P.ldc * P.tsize);
-  P.o_aos = take((size_t)P.tile * rec_per_centre);
   P.o_counts = take((size_t)P.tile * P.nb * 4);
-  // region: one tile of records, or the create-time temporaries
-  size_t t = 0;
-  auto ttake = [&](size_t bytes) { size_t o = t; t += up(bytes); return o; };
-  P.t_raw = ttake(n * 8 * 5);
-  P.t_key_a = ttake(n * 4);
-  P.t_key_b = ttake(n * 4);
-  P.t_idx_a = ttake(n * 4);
-  P.t_idx_b = ttake(n * 4);
-  P.t_inv = ttake(n * 4);
-  P.t_cent64 = ttake((size_t)std::max<int64_t>(P.ncent, 1) * 8);
-  P.t_sort = ttake(P.sort_tmp);
-  if (P.tree_levels > 0) P.t_red = ttake(reduced_scratch_bytes(n));
-  P.region = std::max(t, up((size_t)P.ldc * rec_per_centre));
-  P.o_region = take(P.region);
   P.core = off;
   P.base = off + up(P.pslices * P.slice_bytes);
   // a reduced catalogue has at most n cells, how many is not known before it is built
