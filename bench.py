@@ -26,11 +26,12 @@ sys.path.insert(0, ROOT)
 METRIC = "galaxy-centers/sec for Υ (mixed vs FP64 GPU) + mock p50/p99 latency"
 PEAK_FP32_VALU = 157.3e12     # published vector fp32 peak (packed FMA)
 PEAK_FP64_VALU = 78.6e12      # published vector fp64 peak
+PEAK_VALU_LANES = PEAK_FP32_VALU / 4   # lane instructions/s: 1024 SIMDs x 16 lanes at 2.4 GHz (a packed FMA is 4 flop)
 PEAK_F16_MFMA = 2.5e15        # published dense fp16 / bf16 matrix peak
 PEAK_FP64_MFMA = 78.6e12      # published fp64 matrix peak
 STAGE_A_SRC = os.path.join(ROOT, "paper_2509_07974_amd", "csrc", "stage_a_mfma.hip")
 STAGE_A_INPUT_SRCS = [os.path.join(ROOT, "paper_2509_07974_amd", "csrc", f)
-                      for f in ("api.hip", "cells.hip", "sort.hip")]
+                      for f in ("api.hip", "cells.hip", "sort.hip", "stage_a_plan.hpp", "fpcf4_internal.hpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "stage_a_grf1m_traffic.txt")
 
 
@@ -60,7 +61,8 @@ def kernel_source_hash() -> str:
 
 def input_source_hash() -> str:
     """sha256 over the sources that decide what stage (a) reads: the planner
-    (cell grid), the cell-list build and its sort."""
+    (cell grid), the cell-list build and its sort, the orders and the record
+    and operand layouts."""
     import hashlib
     h = hashlib.sha256()
     for src in STAGE_A_INPUT_SRCS:
@@ -73,6 +75,11 @@ def stage_a_traffic():
     """HBM bytes per stage (a) launch from the committed rocprofv3 counter
     summary, or None if it is missing or was taken on another kernel, planner
     or cell-list source."""
+    return stage_a_counter("traffic_bytes_per_launch")
+
+
+def stage_a_counter(name: str):
+    """An entry of that summary, likewise."""
     try:
         kv = {}
         with open(TRAFFIC_FILE) as f:
@@ -84,7 +91,7 @@ def stage_a_traffic():
             return None
         if kv.get("input_source_sha256") != input_source_hash():
             return None
-        return float(kv["traffic_bytes_per_launch"])
+        return float(kv[name])
     except (OSError, KeyError, ValueError):
         return None
 
@@ -492,17 +499,25 @@ def main():
     launches = max(prof["stage_a_launches"], 1)
     pairs_per_launch = prof["pairs"] / launches
     a_ms = prof["stage_a_ms"] / launches
-    # the mixed paths' kernel contracts on the matrix cores; what limits it is
-    # the vector work that forms their operands, for which no peak is published
+    # The mixed paths' kernel contracts on the matrix cores; what limits it is
+    # the vector work that forms their operands.  Where the committed counters
+    # are of this kernel and workload, the rate is that of its vector lane
+    # instructions; else the algorithmic flops over the vector peak.
     vector = args.precision == "fp64"
-    peak = PEAK_FP64_VALU if vector else PEAK_F16_MFMA
-    achieved = pairs_per_launch * stage_a_flops_per_pair(nmax) / (a_ms * 1e-3)
-    executed = pairs_per_launch * stage_a_flops_executed_per_pair(nmax) / (a_ms * 1e-3)
-    roof = {"bound": "alu" if vector else "mfma", "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
-            "frac": achieved / peak,
-            # the committed counters cover the mixed paths' kernel on grf-1m only
-            "traffic": stage_a_traffic() if args.workload == "grf-1m" and args.precision != "fp64" else None,
+    counted = not vector and args.workload == "grf-1m"
+    valu = stage_a_counter("valu_lane_instructions_per_pair") if counted else None
+    mfma = stage_a_counter("mfma_flops_per_pair") if counted else None
+    rate = pairs_per_launch / (a_ms * 1e-3)
+    peak = PEAK_FP64_VALU if vector else PEAK_VALU_LANES if valu else PEAK_FP32_VALU
+    achieved = rate * (valu or stage_a_flops_per_pair(nmax))
+    executed = rate * stage_a_flops_executed_per_pair(nmax)
+    roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": peak / 1e12,
+            "unit": "T lane instructions/s" if valu else "TFLOP/s", "frac": achieved / peak,
+            "traffic": stage_a_traffic() if counted else None,
             "kernel": "stage_a_kernel (pair multipoles)" if vector else "stage_mm_kernel (pair multipoles)",
+            "algorithmic_tflops": rate * stage_a_flops_per_pair(nmax) / 1e12,
+            "matrix_tflops_issued": rate * mfma / 1e12 if mfma else None,
+            "matrix_frac_issued": rate * mfma / PEAK_F16_MFMA if mfma else None,
             "avg_launch_ms": a_ms, "launches_per_step": launches / steps,
             "pairs_per_launch": pairs_per_launch,
             "flops_per_pair": stage_a_flops_per_pair(nmax),

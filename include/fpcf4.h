@@ -63,8 +63,12 @@ enum { FPCF4_MEM_HOST = 0, FPCF4_MEM_DEVICE = 1 };
 /* Arithmetic of the path.
  *  FPCF4_FP64       : every stage in binary64.
  *  FPCF4_MIXED_FP16 : pair multipoles accumulated in binary32 with blocked
- *                     summation into binary64 (from nmax 4 on over binary16
- *                     hi/lo operands of 22 bits); contraction on MFMA with
+ *                     summation into binary64, from binary32 operands or,
+ *                     4PCF nmax >= 5 and 3PCF nmax 15-22 and >= 25, from
+ *                     operands of 22 bits (two binary16 values each) where the
+ *                     catalogue's weights keep them all at that length, the
+ *                     workspace holds them and the field is not too dense for
+ *                     them to be the faster way; contraction on MFMA with
  *                     fp16 hi/lo split operands and fp32 accumulation per
  *                     centre chunk; binary64 cross-chunk reduction,
  *                     degenerate-term subtraction and output.

@@ -106,10 +106,12 @@ __global__ __launch_bounds__(256) void nat_sum_n2(const double* ups, int nb, int
 // Ubar_mu / Re Nbar, norm[t][a][b] = Re Nbar.  The operands (s, d) are the
 // same for the whole wave and come through scalar loads; the nine
 // correlators' 36 sums share each load of the table.
-// Bound by writing its results: 256 triplets, nmax 10, 129 x 129 angular bins
-// are 579 MB, 122 us at the rate of a copy.  The whole conversion takes 393 us;
-// with a plain sum per output (one thread each, its operands read again for
-// every output) and a division pass over the stored sums it took 1232 us.
+// 256 triplets, nmax 10, 129 x 129 angular bins: 280 us, of which writing the
+// 579 MB of results takes 122 at the rate of a copy.  The rest are the sums: an
+// odd number of bins leaves every second wave with one lane's work (nh = 65).
+// The whole conversion takes 393 us; with a plain sum per output (one thread
+// each, its operands read again for every output) and a division pass over the
+// stored sums it took 1232 us.
 __global__ __launch_bounds__(256) void nat_sum_n3(const double* __restrict__ tmp, int64_t ntrip, int nmax, int nphi,
                                                   const double* __restrict__ table, double* __restrict__ gamma,
                                                   double* __restrict__ norm) {

@@ -50,15 +50,23 @@
 // The unit vector z and its powers 2 and 4 are formed in binary64 from the
 // reciprocal root of one Newton step, and every higher power takes at most
 // three products from those: an error of z^4 in binary32 alone grows eightfold
-// on the way to z^34.  Errors of G against binary64, worst order, relative to
-// its rms: 2.5e-7 to 3.3e-7 at nmax 4 to 16 (vector kernel 5e-7 to 1.6e-6).
+// on the way to z^34.  Errors against binary64, worst order of a family relative
+// to its rms, at nmax 5 to 16 in uniform and clustered catalogues, this kernel
+// / vector kernel: G and Q 2.4e-7 to 3.5e-7 / 5.5e-7 to 1.6e-6, W, A and V
+// 1.6e-7 to 4.3e-7 / 2.4e-7 to 1.4e-6, T_-8 1.5e-7 / 4e-7, T_-4 and M_-4
+// 1.4e-7 / 2.4e-7, U 2.6e-8 / 4.5e-8.  Where no power of z adds to it the
+// operands' 22 bits show: M_0 7.6e-8 to 2.0e-7 / 8.2e-8 to 2.5e-7 (larger in 10
+// of 60 catalogues and orders), and A_2 of the 3PCF plan 1.8e-7 / 1.2e-7; both
+// are same-galaxy terms beside products of G, and every shear correlator of
+// an estimate is closer to binary64 than with the vector kernel.
 //
-// What bounds it: the vector ALUs, some 80 % busy with forming and splitting
-// the operands, at a clock that the card's power limit holds near 2.07 GHz; LDS
-// is 46 % busy and the matrix cores 25 %.  The octets' reads that miss L2 come
-// at 2.2 TB/s, half the rate of a copy.  Three waves per SIMD (168 registers)
-// is what the accumulators leave without spills.  Measured against
-// the vector kernel, 12 bins to 100', nmax 10: 1e6 galaxies 636 ms against 914.
+// What bounds it: the vector ALUs, 79 % of the cycles issuing (220 lane
+// instructions per in-bin pair, 84 % of the candidates of a chunk in the bin),
+// at a clock that the card's power limit holds near 2.1 GHz; LDS is 41 % busy and
+// the matrix cores 24 %.  253 GB miss L2, 0.4 TB/s.  (nmax 15, 8192 of 1e7
+// galaxies: 65, 36 and 23 %.)  Three waves per SIMD (168 registers) is what
+// the accumulators leave without spills.  Measured against the vector kernel,
+// 12 bins to 100', nmax 10: 1e6 galaxies 613 ms against 914.
 #include <algorithm>
 #include <type_traits>
 
@@ -81,8 +89,10 @@ constexpr int DPP_ROW_ROR8 = 0x128;  // lane i <- i xor 8 within 16
 // together, so a block's partial sums are far larger than the bin's sum after
 // cancellation, and every matrix product rounds at their size: with blocks of
 // 16 chunks the multipoles W of a dense field had errors of 6.5e-7 of their rms
-// (nmax 4 to 10), with 4 up to 3.4e-7 and with 2 1.8e-7; the vector kernel has
-// 2e-7 to 8e-7, growing with the order.  The lower orders get the shorter blocks.
+// (at every order up to nmax 10), with 4 up to 3.4e-7 and with 2 1.8e-7; the vector
+// kernel has 2e-7 to 8e-7, growing with the order.  The lower orders get the
+// shorter blocks.  The low-part accumulators stay in binary32 over the whole
+// bin: their sums, and with them their roundings, are 2^-11 of the others'.
 constexpr int fold_chunks(int n) { return nord(n) <= 6 ? 2 : 4; }
 
 // row orders p > 0 of a plan
