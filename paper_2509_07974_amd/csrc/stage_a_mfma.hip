@@ -839,25 +839,33 @@ __global__ __launch_bounds__(256) void octet_kernel(const Rec* gal, int64_t n, M
     const bool low = (row & 1) != 0;
     const int f = row < 16 ? imin(row >> 1, NF - 1) : NF + ((row - 16) >> 1);
     const bool none = row == 14 || row == 15;
+    const double scale = 1.0 / ms.inv[f];   // exact: a power of two
+    const bool judge = !low && !none && !second_part(f), pair = judge && complex_weight(f);
+    const double scale2 = pair ? 1.0 / ms.inv[f + 1] : 0.0;
+    double most = 0.0;   // of a real or complex weight
     half8v v;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int64_t q = 8 * oc + j;
       float x = 0.f;
-      if (q < n && !none) x = (float)(weight_of(gal[q], f) / ms.inv[f]);   // exact: a power of two
+      if (q < n && !none) {
+        const double s = weight_of(gal[q], f) * scale;
+        x = (float)s;
+        most = fmax(most, fabs(s));
+        if (pair) most = fmax(most, fabs(weight_of(gal[q], f + 1) * scale2));
+      }
       const _Float16 h = (_Float16)x;
       v[j] = low ? (_Float16)(x - (float)h) : h;
     }
     *reinterpret_cast<half8v*>(o + 128 + 16 * row) = v;
-    if (!low && !none && !second_part(f)) {
-      // the largest of a real or complex weight; a last octet of fewer than
-      // eight counts with the one before it, since a galaxy or two alone may
-      // well have a small shear
-      double most = 0.0;
-      for (int64_t q = 8 * oc + 8 > n && oc > 0 ? 8 * oc - 8 : 8 * oc; q < 8 * oc + 8 && q < n; ++q) {
-        most = fmax(most, fabs(weight_of(gal[q], f) / ms.inv[f]));
-        if (complex_weight(f)) most = fmax(most, fabs(weight_of(gal[q], f + 1) / ms.inv[f + 1]));
-      }
+    if (judge && most < OCTET_MIN) {
+      // a last octet of fewer than eight counts with the one before it, since a
+      // galaxy or two alone may well have a small shear
+      if (8 * oc + 8 > n && oc > 0)
+        for (int64_t q = 8 * oc - 8; q < 8 * oc; ++q) {
+          most = fmax(most, fabs(weight_of(gal[q], f) * scale));
+          if (pair) most = fmax(most, fabs(weight_of(gal[q], f + 1) * scale2));
+        }
       if (most > 0.0 && most < OCTET_MIN) *faint = 1u;   // every writer stores the same
     }
   }
