@@ -99,16 +99,12 @@ __global__ __launch_bounds__(256) void stats_final_kernel(const double* part, in
   stat_block(v);
   if (threadIdx.x == 0)
     for (int k = 0; k < kPartStats; ++k) out[k] = v[k];
-  __shared__ int occ[256];
+  if (threadIdx.x >= 64) return;
   int c = 0;
-  for (int q = (int)threadIdx.x; q < kCoarseWords; q += 256) c += __popc(coarse[q]);
-  occ[threadIdx.x] = c;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) occ[threadIdx.x] += occ[threadIdx.x + st];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[kPartStats] = occ[0];
+  for (int q = (int)threadIdx.x; q < kCoarseWords; q += 64) c += __popc(coarse[q]);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);
+  if (threadIdx.x == 0) out[kPartStats] = c;
 }
 
 __device__ __forceinline__ int cell_of(double v, double v0, double inv_h, int nc) {

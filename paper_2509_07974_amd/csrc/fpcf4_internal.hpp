@@ -120,7 +120,7 @@ __host__ __device__ inline BinTiles bin_tiles(int nb) {
 // sum |w g|^2, sum w^2, occupied coarse cells.  The last are counted in a bitmap
 // of kCoarse x kCoarse cells that the plane is folded onto.
 constexpr int kCatStats = 9;
-constexpr int kCoarse = 256;
+constexpr int kCoarse = 128;
 constexpr int kCoarseWords = kCoarse * kCoarse / 32;
 
 // Sorted catalogue on the device.
