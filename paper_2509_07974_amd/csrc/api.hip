@@ -322,6 +322,7 @@ struct fpcf4_request {
   char* ws = nullptr;
   Grid grid{};
   std::vector<double> edges;
+  double density = 0.0;                     // galaxies per unit of occupied area
   bool mm[TREE_LEVELS_MAX + 1] = {};        // octets built for the galaxies / reduced catalogue d
   MatScale ms[TREE_LEVELS_MAX + 1] = {};
   std::vector<char> stepped;
@@ -515,6 +516,7 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
   const bool folded = std::max(wx, wy) > (kCoarse - 1) * coarse;
   const double occupied = folded ? -bits * std::log1p(-bb[8] / bits) : bb[8];
   const double area = std::min(wx * wy, occupied * coarse * coarse);
+  R->density = area > 0.0 ? (double)n / area : 0.0;
   double h = std::max(rmax / 48.0, std::min(1.35 * std::sqrt(area / (double)n), coarse));
   for (;;) {
     const double ncx = std::floor(wx / h) + 1.0, ncy = std::floor(wy / h) + 1.0;
@@ -597,6 +599,7 @@ void matrix_args(const fpcf4_request* R, StageAArgs& a) {
     a.ms[d] = R->ms[d];
   }
   a.host_edges = R->edges.data();
+  a.density = R->density;
 }
 
 fpcf4_status request_step(fpcf4_request* R, int64_t tile, bool stage_b) {

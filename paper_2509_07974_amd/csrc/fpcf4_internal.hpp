@@ -210,7 +210,9 @@ struct StageAArgs {
   const void* octets[TREE_LEVELS_MAX + 1];
   MatScale ms[TREE_LEVELS_MAX + 1];
   const double* host_edges;                  // host copy of edges, for the launcher
+  double density;                            // galaxies per unit area, likewise
   int32_t ngroups;                           // bin groups, set by the launcher
+  int32_t block;                             // centres that take them in turn, likewise
   uint8_t gfirst[FPCF4_NBINS_SUPPORTED + 1], gend[FPCF4_NBINS_SUPPORTED + 1];
 };
 

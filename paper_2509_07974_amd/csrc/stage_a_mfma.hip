@@ -26,14 +26,12 @@
 // Mapping on CDNA4 (wave64):
 //  * one wave owns one (centre, group of bins) at a time (per-XCD queues over
 //    the Morton-ordered centre list, with stealing); no barriers between
-//    waves.  The widest bins come first and all centres of a queue take the
-//    same group of bins together, so that the waves of an XCD read the same
-//    galaxies at the same time: the octets are 96 bytes a galaxy, and in a dense
-//    field one row of cells of one group is as large as a share of L2.  With
-//    the groups in turn within blocks of 64 centres, six groups were in flight
-//    at once (1e6 galaxies, 12 bins to 100', nmax 8, 65536 or 16384 centres at 3,
-//    10, 60 and 120 galaxies per square arcmin: 52, 189, 134 and 197 ms, against
-//    48, 172, 111 and 162 now);
+//    waves.  The centres of a block take the groups in turn, the widest bins
+//    first.  Where the octets around a centre do not fit the L2 of an XCD, the
+//    block is the whole queue, so that its waves read the same galaxies at the
+//    same time: the octets are 96 bytes a galaxy, and in a dense field one row
+//    of cells of one group is as large as a share of L2.  Elsewhere it is 64
+//    centres, so that units of several lengths overlap (launch_pairs_mm);
 //  * the annulus is a list of octets (8 consecutive sorted galaxies, aligned)
 //    with an 8-bit mask of those inside the row segment.  A chunk is 8
 //    octets: lane l forms neighbour l&7 of octet l>>3.  r^2 is formed in
@@ -376,9 +374,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void s
       const int hi = (int)(((int64_t)a.ncent * (xcd + 1)) >> 3);
       const unsigned u = (unsigned)__builtin_amdgcn_readfirstlane(next);
       if (u < (unsigned)(hi - lo) * (unsigned)ng) {
-        const unsigned nc = (unsigned)(hi - lo);
-        grp = (int)(u / nc);
-        idx = lo + (int)(u - (unsigned)grp * nc);
+        const unsigned per = (unsigned)a.block * (unsigned)ng, blk = u / per, rem = u - blk * per;
+        const int b0 = lo + (int)(blk * (unsigned)a.block);
+        const unsigned nc = (unsigned)imin(a.block, hi - b0);
+        grp = (int)(rem / nc);
+        idx = b0 + (int)(rem - (unsigned)grp * nc);
         next = request();
         break;
       }
@@ -754,6 +754,14 @@ hipError_t launch_pairs_mm(StageAArgs a, hipStream_t s) {
     a.gfirst[q] = (uint8_t)cut[q + 1];
     a.gend[q] = (uint8_t)cut[q];
   }
+  // Octets within the outermost radius of a centre, against 4 MB of L2.  1e6
+  // galaxies, 12 bins to 100', nmax 8, at 3, 10, 60 and 120 per square arcmin
+  // (9 MB and more): 52, 189, 134 and 197 ms with blocks of 64, where six groups are
+  // in flight at once, 48, 172, 111 and 162 with the whole queue; at 1 (3 MB) 22.1
+  // and 21.5, at 0.5 15.7 and 16.1, and 30011 galaxies at 1, 13 bins to 57' (1 MB)
+  // 3.06 and 3.12.
+  const double near = a.density * M_PI * e[a.nb] * e[a.nb] * (OCTET_BYTES / 8.0);
+  a.block = near > 2.5e6 ? imax(a.ncent, 1) : 64;
   const int resident = resident_blocks_mm<N, RED>();
   const int64_t units = (int64_t)a.ncent * a.ngroups;
   int nblocks = (int)std::min<int64_t>((units + 3) / 4, resident);
