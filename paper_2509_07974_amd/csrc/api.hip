@@ -412,8 +412,7 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
     at += up(b);
     return p;
   };
-  bool octets = false;
-  for (int d = 0; d <= P.tree_levels; ++d) octets |= (R->octets[d] = room(P.octets[d])) != nullptr;
+  for (int d = 0; d <= P.tree_levels; ++d) R->octets[d] = room(P.octets[d]);
   int32_t* order_buf = reinterpret_cast<int32_t*>(room(P.order_bytes));
   R->ppart = reinterpret_cast<double*>(R->ws + at);
   R->slices = P.pslices;
@@ -585,10 +584,7 @@ fpcf4_status request_init(const fpcf4_catalogue* cat, const fpcf4_bins* bins,
       R->mm[d] = true;
     }
   }
-  unsigned faint[TREE_LEVELS_MAX + 1] = {};
-  if (octets) HIPCHK(hipMemcpyAsync(faint, R->ws + P.o_faint, sizeof faint, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  for (int d = 0; d <= TREE_LEVELS_MAX; ++d) R->mm[d] = R->mm[d] && !faint[d];
   return FPCF4_OK;
 }
 
@@ -598,6 +594,7 @@ void matrix_args(const fpcf4_request* R, StageAArgs& a) {
     a.octets[d] = R->mm[d] ? R->octets[d] : nullptr;
     a.ms[d] = R->ms[d];
   }
+  a.faint = R->at<unsigned>(R->P.o_faint);
   a.host_edges = R->edges.data();
   a.density = R->density;
 }

@@ -181,6 +181,7 @@ hipError_t build_octets(const Rec* gal, int64_t n, const MatScale& ms, void* out
 constexpr int SCHED_STRIDE = 32;                  // words between the counters of two XCDs
 constexpr int SCHED_WORDS = 8 * SCHED_STRIDE;     // counters of one launch
 
+enum { RUN_ALWAYS = 0, RUN_UNLESS_FAINT, RUN_IF_FAINT };
 struct StageAArgs {
   SortedCat cat;
   const int32_t* centres;   // positions in cgal of this tile's centres
@@ -209,6 +210,12 @@ struct StageAArgs {
   // galaxies (0) and of reduced catalogue d; null: the vector kernel
   const void* octets[TREE_LEVELS_MAX + 1];
   MatScale ms[TREE_LEVELS_MAX + 1];
+  // build_octets' findings for the galaxies and reduced catalogue d, known to the
+  // device only; a launch that depends on them: the catalogues that it reads
+  // (bit d), and whether it runs if one of them is faint or unless
+  const unsigned* faint;
+  unsigned faint_of;
+  int8_t when;                               // RUN_ALWAYS, RUN_UNLESS_FAINT, RUN_IF_FAINT
   const double* host_edges;                  // host copy of edges, for the launcher
   double density;                            // galaxies per unit area, likewise
   int32_t ngroups;                           // bin groups, set by the launcher

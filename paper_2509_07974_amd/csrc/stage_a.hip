@@ -906,6 +906,7 @@ __device__ __forceinline__ void dispatch(int wv, const StageAArgs& a,
 template <typename T, int N, bool RED>
 __global__ __launch_bounds__((64 * Conf<T, N>::W)) __attribute__((amdgpu_waves_per_eu(Conf<T, N>::EU))) void stage_a_kernel(StageAArgs a) {
   __shared__ Shared<T, Conf<T, N>::W, Conf<T, N>::NMX, RED> sh;
+  if (ruled_out(a)) return;
   // wave index as a scalar, so each wave branches to its own pass only
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   dispatch<T, N, 0, RED>(wv, a, sh, lane_id());
@@ -1043,6 +1044,24 @@ static hipError_t launch_pairs(const StageAArgs& a, hipStream_t s) {
 template <int N, bool RED>
 hipError_t launch_pairs_mm(StageAArgs a, hipStream_t s);
 
+// binary32: on the matrix cores where the caller built octets (see matrix_scale
+// in api.hip), else on the vector ALUs.  Whether the octets hold the weights is
+// known to the device alone, and asking it would cost a small call more (25 us
+// of 370) than a second launch that ends at once (6).
+template <typename T, int N, bool RED>
+static hipError_t launch_either(StageAArgs a, bool octets, unsigned catalogues, hipStream_t s) {
+  if constexpr (sizeof(T) == 4 && use_matrix(N)) {
+    if (octets) {
+      a.faint_of = catalogues;
+      a.when = RUN_UNLESS_FAINT;
+      const hipError_t e = launch_pairs_mm<N, RED>(a, s);
+      if (e != hipSuccess) return e;
+      a.when = RUN_IF_FAINT;
+    }
+  }
+  return launch_pairs<T, N, RED>(a, s);
+}
+
 // The discrete bins (level 0) in one launch and, with the tree
 // approximation, the bins on reduced catalogues in a second one (its own
 // scheduling counters); then the relayout of all records.
@@ -1059,22 +1078,19 @@ hipError_t launch_n(const StageAArgs& a, hipStream_t s, int* nlaunch, hipEvent_t
   ae.b_hi = k;
   ar.b_lo = k;
   *nlaunch = 0;
-  // binary32: on the matrix cores where the caller built octets (see
-  // matrix_scale in api.hip), else on the vector ALUs
-  const bool mm = a.octets[0] != nullptr;
-  bool mmr = true;
-  for (int b = k; b < a.b_hi; ++b) mmr = mmr && a.octets[a.level[b]] != nullptr;
-  constexpr bool matrix = sizeof(T) == 4 && use_matrix(N);
-  hipError_t e;
-  if constexpr (matrix) e = mm ? launch_pairs_mm<N, false>(ae, s) : launch_pairs<T, N, false>(ae, s);
-  else e = launch_pairs<T, N, false>(ae, s);
+  bool octets = true;   // of every reduced catalogue in use
+  unsigned reduced = 0;
+  for (int b = k; b < a.b_hi; ++b) {
+    octets = octets && a.octets[a.level[b]] != nullptr;
+    reduced |= 1u << a.level[b];
+  }
+  hipError_t e = launch_either<T, N, false>(ae, a.octets[0] != nullptr, 1u, s);
   if (e != hipSuccess) return e;
   *nlaunch = 1;
   if (red) {
     if constexpr (sizeof(T) == 4) {
       ar.work_counter = a.work_counter + SCHED_WORDS;
-      if constexpr (matrix) e = mmr ? launch_pairs_mm<N, true>(ar, s) : launch_pairs<T, N, true>(ar, s);
-      else e = launch_pairs<T, N, true>(ar, s);
+      e = launch_either<T, N, true>(ar, octets, reduced, s);
       if (e != hipSuccess) return e;
       *nlaunch = 2;
     } else {

@@ -324,6 +324,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void s
   __shared__ WaveBuf<N> bufs[4];
   __shared__ unsigned bmax[2][FPCF4_NBINS_SUPPORTED];
   __shared__ double unscale[TREE_LEVELS_MAX + 1][NWEIGHTS + 4];
+  if (ruled_out(a)) return;
 
   const unsigned lane = lane_id();
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));

@@ -65,6 +65,16 @@ __device__ __forceinline__ unsigned rank_in_mask(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
+// Whether a launch is the one that findings of faint octets rule out (the same
+// for every workgroup of it).
+__device__ __forceinline__ bool ruled_out(const StageAArgs& a) {
+  if (a.when == RUN_ALWAYS) return false;
+  bool faint = false;
+  for (int d = 0; d <= TREE_LEVELS_MAX; ++d)
+    if ((a.faint_of >> d & 1u) != 0u) faint |= a.faint[d] != 0u;
+  return faint != (a.when == RUN_IF_FAINT);
+}
+
 // Plans that the matrix-core kernel serves.
 __host__ __device__ constexpr bool use_matrix(int n) { return matrix_order(is3(n) ? 3 : 4, nord(n)); }
 
