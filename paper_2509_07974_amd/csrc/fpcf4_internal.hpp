@@ -150,12 +150,15 @@ __host__ __device__ constexpr bool matrix_order(int order, int n) {
 // it serves those orders.  In a dense field it waits for its operands, 96 bytes a
 // neighbour where the vector kernel reads 32, and is no faster at one order than
 // at the next, so that the vector kernel is ahead at the lower ones.  Stage
-// (a) of 16384 centres of 1e6 galaxies, 12 bins to 100', vector / matrix kernel:
-// 4PCF nmax 5 at 10, 20, 30 and 80 galaxies per square arcmin 177 / 171 (65536
-// centres), 258 / 257 (likewise), 106 / 107, 142 / 152, nmax 6 at 80 and 120 153 / 152, 156 / 164, nmax 7
-// at 120 165 / 161; 3PCF records of order 8 at 1, 3 and 30 5.0 / 4.9, 11.5 /
-// 12.0, 101 / 106, of order 9 at 30 and 60 106 / 106, 124 / 128, of order 10 at
-// 60 and 120 132 / 129, 135 / 138, of order 11 at 120 139 / 139.
+// (a) of 16384 centres of 1e6 galaxies (65536 where 4PCF at 20 and less), 12
+// bins to 100', at some galaxies per square arcmin, vector / matrix kernel, ms:
+//   4PCF nmax 5      10: 177 / 171   20: 258 / 257   30: 106 / 107   80: 142 / 152
+//   4PCF nmax 6      80: 153 / 152  120: 156 / 164
+//   4PCF nmax 7     120: 165 / 161
+//   3PCF order 8      1: 5.0 / 4.9    3: 11.5 / 12.0  30: 101 / 106
+//   3PCF order 9     30: 106 / 106   60: 124 / 128
+//   3PCF order 10    60: 132 / 129  120: 135 / 138
+//   3PCF order 11   120: 139 / 139
 __host__ __device__ constexpr double matrix_density_max(int order, int n) {
   if (order == 3) return n == 8 ? 2e4 : n == 9 ? 2e5 : n == 10 ? 8e5 : 1e300;
   return n == 5 ? 1.5e5 : n == 6 ? 8e5 : 1e300;

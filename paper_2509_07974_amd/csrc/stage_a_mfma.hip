@@ -60,11 +60,12 @@
 //
 // What bounds it: the vector ALUs, 79 % of the cycles issuing (220 lane
 // instructions per in-bin pair, 84 % of the candidates of a chunk in the bin),
-// at a clock that the card's power limit holds near 2.1 GHz; LDS is 41 % busy and
-// the matrix cores 24 %.  253 GB miss L2, 0.4 TB/s.  (nmax 15, 8192 of 1e7
-// galaxies: 65, 36 and 23 %.)  Three waves per SIMD (168 registers) is what
-// the accumulators leave without spills.  Measured against the vector kernel,
-// 12 bins to 100', nmax 10: 1e6 galaxies 613 ms against 914.
+// at a clock that the card's power limit holds between 2.0 and 2.1 GHz; LDS is
+// 41 % busy and the matrix cores 24 %.  258 GB miss L2, 0.4 TB/s.  (nmax 15, 8192
+// of 1e7 galaxies: 66, 37 and 24 %.)  Three waves per SIMD (168 registers) is
+// what the accumulators leave without spills.  Measured against the vector
+// kernel, 12 bins to 100', nmax 10: 1e6 galaxies 613 ms at 2.11 GHz, 647 at 2.00,
+// against 914 at 2.37.
 #include <algorithm>
 #include <type_traits>
 
